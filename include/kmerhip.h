@@ -275,7 +275,8 @@ typedef struct kh_contigs kh_contigs;
  * kh_contigs_free.  Besides the sequences the contigs keep the contig of
  * every row of t (4 bytes per row), which kh_prune and kh_localize_reads
  * use.  KH_EINVAL for a table of a destroyed context or another device,
- * KH_ENOMEM if the working set (about 70 bytes per row) does not fit. */
+ * KH_ENOMEM if the working set (about 40 bytes per row, up to 115 where
+ * nearly every row ends a contig) does not fit. */
 int kh_traverse(kh_ctx *ctx, const kh_table *t, void *hip_stream,
                 kh_contigs **out);
 

@@ -403,6 +403,11 @@ int finish_rows(kh_ctx* ctx, unsigned long long* ctr, uint8_t* table,
                 uint64_t cap, const kh_params& p, const RecountFn& recount,
                 hipStream_t s, kh_table* t);
 int check_params(const kh_params* p);
+// Index of n sorted rows (n < 2^32 - 1) by their top key bits, in `start`
+// (stream-ordered; kh_rows.hpp).
+struct RowIndex;
+int row_index_build(Pool* pool, const uint64_t* keys, int64_t n, uint32_t k,
+                    Buf<uint32_t>& start, RowIndex* ix, hipStream_t s);
 // Pack a read set and count one k into an existing table object (whose rows
 // may go to the caller's buffers, kh_table::dst_cap); no streamed upload.
 int count_into(kh_ctx* ctx, const kh_reads* reads, const kh_params& p, hipStream_t s,

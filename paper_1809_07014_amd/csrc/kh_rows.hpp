@@ -1,7 +1,8 @@
 // Device helpers over exported rows (keys of W words, most significant
 // first, the k-mer right-aligned in 2k bits, rows in ascending key order):
-// one-base shifts of a k-mer and binary search over sorted rows.  Used by
-// the traversal, merge and pruning kernels.
+// one-base shifts of a k-mer, binary search over sorted rows, and lookups
+// through an index of the rows by their top key bits.  Used by the traversal,
+// merge, pruning and localisation kernels.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -49,6 +50,45 @@ __device__ __forceinline__ int64_t lower_bound_rows(const uint64_t* keys, int64_
       hi = mid;
   }
   return lo;
+}
+
+// Index of sorted rows by the top `bits` bits of the 2k-bit key: the rows of
+// prefix p are [start[p], start[p + 1]) (2^bits + 1 entries).  The rows are
+// sorted already, so it is built by one streaming pass over the keys (no
+// hashing, no atomics), and a lookup costs one entry pair and the few rows of
+// its bucket (kh_rowindex.hip).
+struct RowIndex {
+  const uint32_t* start;
+  int bits;  // 1 .. 32, at most 2k
+};
+
+// The top `bits` bits of a key whose word 0 holds `top` bits.
+template <int W>
+__device__ __forceinline__ uint32_t row_prefix(const uint64_t* w, int top, int bits) {
+  if (W == 1 || bits <= top) return (uint32_t)(w[0] >> (top - bits));
+  const int low = bits - top;  // bits of word 1, 1 .. 31
+  return (uint32_t)((w[0] << low) | (w[W > 1 ? 1 : 0] >> (64 - low)));
+}
+
+// Row of key q, or -1.
+template <int W>
+__device__ __forceinline__ int64_t find_row(const uint64_t* keys, const RowIndex& ix, int top,
+                                            const uint64_t (&q)[W]) {
+  const uint32_t p = row_prefix<W>(q, top, ix.bits);
+  int64_t lo = ix.start[p], hi = ix.start[(uint64_t)p + 1];
+  while (lo < hi) {
+    const int64_t mid = lo + (hi - lo) / 2;
+    uint64_t w[W];  // the whole row at once: one round trip per probe
+#pragma unroll
+    for (int j = 0; j < W; ++j) w[j] = keys[mid * W + j];
+    const int c = cmp_rows<W>(w, q);
+    if (c == 0) return mid;
+    if (c < 0)
+      lo = mid + 1;
+    else
+      hi = mid;
+  }
+  return -1;
 }
 
 }  // namespace kh
