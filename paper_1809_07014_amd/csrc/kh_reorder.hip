@@ -101,19 +101,43 @@ __global__ __launch_bounds__(kRB) void k_order_lens(const int64_t* offsets, int6
   lens[i] = (uint64_t)(offsets[r + 1] - offsets[r]);
 }
 
-// One wave per read copies its bases and qualities to its new place.
+// 16 bytes from a to b (any alignment).
+__device__ __forceinline__ void copy16(const uint8_t* a, uint8_t* b) {
+  uint4 v;
+  __builtin_memcpy(&v, a, 16);
+  __builtin_memcpy(b, &v, 16);
+}
+
+// 16 lanes per read copy its bases and qualities to its new place, 16 bytes a
+// lane; the last piece of a read is its last 16 bytes, over the one before.
+//
+// Bound by the three dependent loads of a read (order, offsets, bytes): four
+// reads a wave keep more of them in flight.  4e6 reads of 150 bases (2.4 GB
+// moved): 0.70 ms (2.36 ms with a wave per read and a byte per lane).
+constexpr int kGatherLanes = 16;
+
 __global__ __launch_bounds__(kRB) void k_gather_bytes(const uint8_t* seq, const uint8_t* qual,
                                                       const int64_t* offsets, int64_t n,
                                                       const int64_t* order,
                                                       const int64_t* new_off, uint8_t* o_seq,
                                                       uint8_t* o_qual) {
-  const int64_t i = (int64_t)blockIdx.x * (kRB / 64) + (threadIdx.x >> 6);
+  const int64_t i =
+      (int64_t)blockIdx.x * (kRB / kGatherLanes) + (threadIdx.x / kGatherLanes);
   if (i >= n) return;
   const int64_t r = order[i];
   const int64_t src = offsets[r], len = offsets[r + 1] - src, dst = new_off[i];
-  for (int64_t p = threadIdx.x & 63; p < len; p += 64) {
-    o_seq[dst + p] = seq[src + p];
-    o_qual[dst + p] = qual[src + p];
+  const int lane = threadIdx.x % kGatherLanes;
+  if (len < 16) {
+    if (lane < len) {
+      o_seq[dst + lane] = seq[src + lane];
+      o_qual[dst + lane] = qual[src + lane];
+    }
+    return;
+  }
+  for (int64_t p = 16 * lane; p < len; p += 16 * kGatherLanes) {
+    const int64_t at = p + 16 <= len ? p : len - 16;
+    copy16(seq + src + at, o_seq + dst + at);
+    copy16(qual + src + at, o_qual + dst + at);
   }
 }
 
@@ -148,8 +172,8 @@ int gather_reads_ordered(Pool* pool, const uint8_t* seq, const uint8_t* qual,
     return fail(KH_EINVAL, "order is not a permutation (bases %llu, expected %lld)",
                 (unsigned long long)h[0], (long long)total);
   HIP_TRY(hipMemcpyAsync(o_off + n_reads, scal.p, 8, hipMemcpyDeviceToDevice, s));
-  hipLaunchKernelGGL(k_gather_bytes, dim3(rgrid(n_reads, kRB / 64)), dim3(kRB), 0, s, seq, qual,
-                     offsets, n_reads, order, o_off, o_seq, o_qual);
+  hipLaunchKernelGGL(k_gather_bytes, dim3(rgrid(n_reads, kRB / kGatherLanes)), dim3(kRB), 0,
+                     s, seq, qual, offsets, n_reads, order, o_off, o_seq, o_qual);
   HIP_TRY(hipGetLastError());
   HIP_TRY(hipStreamSynchronize(s));
   return KH_OK;
