@@ -22,6 +22,7 @@
 #include <vector>
 
 #include "kh_host.hpp"
+#include "kh_rows.hpp"
 
 using namespace kh;
 
@@ -102,6 +103,8 @@ int kh::check_params(const kh_params* p) {
     return fail(KH_EINVAL, "owner %u is not below owner_shards %u", p->owner, p->owner_shards);
   return KH_OK;
 }
+
+static void start_timing(kh_ctx* ctx);
 
 static int set_device(kh_ctx* ctx) {
   HIP_TRY(hipSetDevice(ctx->device));
@@ -1016,6 +1019,103 @@ int kh::count_into(kh_ctx* ctx, const kh_reads* reads, const kh_params& p, hipSt
   Packed pk(&ctx->pool);
   KH_TRY(pack_reads(ctx, reads, p, s, pk, false));
   return count_packed_into(ctx, pk, p, s, t);
+}
+
+// The windows whose key is none of the given rows, counted in a table planned
+// for as many keys as there are such windows.  They take the place of the
+// windows a Bloom pass has seen: the counting pass's sighting bits, beside a
+// filter that holds nothing.
+int kh::count_absent(kh_ctx* ctx, const kh_reads* reads, const kh_params& p,
+                     const uint64_t* keys, const RowIndex& ix, hipStream_t s, kh_table* t) {
+  KH_TRY(check_params(&p));
+  Packed pk(&ctx->pool);
+  start_timing(ctx);
+  KH_TRY(pack_reads(ctx, reads, p, s, pk, false));
+  std::memset(ctx->last_stats, 0, sizeof ctx->last_stats);
+  if (pk.n == 0) {
+    HIP_TRY(hipStreamSynchronize(s));
+    return KH_OK;
+  }
+  Pool* pool = &ctx->pool;
+  const SlotLayout lay = slot_layout(table_chunks(p.k));
+  launch_reset_ctr(ctx->ctr, kStatusBadOffsets, s);
+  Buf<uint64_t> bloom(pool), seen(pool);
+  constexpr uint64_t kNoBloom = 64;
+  KH_TRY(bloom.alloc(kNoBloom));
+  launch_fill_u64(bloom.p, kNoBloom, 0ull, s);
+  KH_TRY(seen.alloc((uint64_t)((pk.n + kTile - 1) / kTile) * (kTile / 64)));
+  AbsentArgs aa{};
+  aa.bases = pk.bases.p;
+  aa.hq = pk.hq.p;
+  aa.bad = pk.bad.p;
+  aa.st = pk.st.p;
+  aa.base_words = pk.base_words;
+  aa.plane_words = pk.plane_words;
+  aa.n = pk.n;
+  aa.k = p.k;
+  aa.keys = keys;
+  aa.absent = seen.p;
+  aa.ctr = ctx->ctr;
+  launch_absent(aa, ix, ctx->cus * 8, s);
+  HIP_TRY(hipGetLastError());
+  uint64_t c[kCtrCount];
+  KH_TRY(read_ctr(ctx, s, c));
+  if (c[kCtrStatus] & kStatusBadOffsets)
+    return fail(KH_EINVAL, "offsets are not non-decreasing from 0 to the base count");
+  const uint64_t n_windows = c[kCtrWindows], n_absent = c[kCtrPassed];
+  if (n_windows > 0xffffffffull)
+    return fail(KH_EOVERFLOW, "%llu windows in one table exceed the 32-bit count",
+                (unsigned long long)n_windows);
+  t->n_windows = n_windows;
+  ctx->last_stats[4] = n_windows;
+  ctx->last_stats[8] = n_absent;
+  ctx->last_stats[10] = p.k;
+  if (n_absent == 0) return KH_OK;
+
+  WindowArgs wa{};
+  wa.bases = pk.bases.p;
+  wa.hq = pk.hq.p;
+  wa.bad = pk.bad.p;
+  wa.st = pk.st.p;
+  wa.base_words = pk.base_words;
+  wa.plane_words = pk.plane_words;
+  wa.n = pk.n;
+  wa.k = p.k;
+  wa.ctr = ctx->ctr;
+  wa.tiles_per_block = (int)ctx->tune.tiles_per_block;
+  wa.lanes = (int)ctx->tune.count_lanes;
+  wa.bloom = bloom.p;
+  wa.bloom_blocks = kNoBloom;
+  wa.seen = seen.p;
+  Buf<uint8_t> table(pool);
+  uint64_t cap = (uint64_t)std::ceil((double)(n_absent + 1024) / (double)p.load_factor);
+  for (int retry = 0;; ++retry, cap *= 2) {
+    if (cap >= (1ull << 32))
+      return fail(KH_ENOMEM, "table capacity %llu exceeds 2^32 slots", (unsigned long long)cap);
+    KH_TRY(table.alloc(cap * lay.stride));
+    launch_fill_u64(reinterpret_cast<uint64_t*>(table.p), cap * lay.stride / 8, 0ull, s);
+    launch_reset_ctr(ctx->ctr, 0, s);
+    wa.table = table.p;
+    wa.capacity = cap;
+    wa.max_probe = (uint32_t)std::min<uint64_t>(cap, 1u << 14);
+    launch_windows(wa, 2, s);
+    HIP_TRY(hipGetLastError());
+    KH_TRY(read_ctr(ctx, s, c));
+    ctx->last_stats[6] = (uint64_t)retry;
+    if (!(c[kCtrStatus] & kStatusProbeLimit)) break;
+  }
+  ctx->last_stats[0] = cap;
+  ctx->last_stats[1] = c[kCtrClaimed];
+  ctx->last_stats[7] = cap * lay.stride;
+  RecountFn recount = [&](HeavyEntry* heavy, uint32_t* index, uint32_t mask) -> int {
+    WindowArgs wh = wa;
+    wh.heavy = heavy;
+    wh.heavy_index = index;
+    wh.heavy_mask = mask;
+    launch_windows(wh, 3, s);
+    return KH_OK;
+  };
+  return finish_rows(ctx, ctx->ctr, table.p, cap, p, recount, s, t);
 }
 
 // Batched multi-k: fused Bloom launches (one per key width; for streamed

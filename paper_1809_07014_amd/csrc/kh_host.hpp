@@ -408,6 +408,25 @@ int check_params(const kh_params* p);
 struct RowIndex;
 int row_index_build(Pool* pool, const uint64_t* keys, int64_t n, uint32_t k,
                     Buf<uint32_t>& start, RowIndex* ix, hipStream_t s);
+// Contig windows that are no rows of a table (kh_merge.hip): a bit per window
+// start in `absent` (every word of the tiles is written), the valid windows in
+// ctr[kCtrWindows] and the absent ones in ctr[kCtrPassed].
+struct AbsentArgs {
+  const uint64_t* bases;
+  const uint64_t* hq;
+  const uint64_t* bad;
+  const uint64_t* st;
+  int64_t base_words, plane_words, n;
+  uint32_t k;
+  const uint64_t* keys;  // the table's rows
+  uint64_t* absent;
+  unsigned long long* ctr;
+};
+void launch_absent(const AbsentArgs& a, const RowIndex& ix, int blocks, hipStream_t s);
+// Pack a read set and count into t its windows whose key is none of the rows
+// `keys` (indexed by ix).
+int count_absent(kh_ctx* ctx, const kh_reads* reads, const kh_params& p, const uint64_t* keys,
+                 const RowIndex& ix, hipStream_t s, kh_table* t);
 // Pack a read set and count one k into an existing table object (whose rows
 // may go to the caller's buffers, kh_table::dst_cap); no streamed upload.
 int count_into(kh_ctx* ctx, const kh_reads* reads, const kh_params& p, hipStream_t s,
