@@ -505,6 +505,10 @@ static int count_owned(kh_ctx* ctx, Packed& pk, const kh_params& p, hipStream_t 
   KH_TRY(h1.alloc((uint64_t)nb1 * grid));
   KH_TRY(b1.alloc((uint64_t)nb1));
   KH_TRY(part.alloc(scan_tmp_words((int64_t)nb1 * grid)));
+  Buf<uint64_t> win(pool), lx(pool), rx(pool);
+  KH_TRY(win.alloc((uint64_t)pk.plane_words));
+  KH_TRY(lx.alloc((uint64_t)pk.plane_words));
+  KH_TRY(rx.alloc((uint64_t)pk.plane_words));
   OwnRouteArgs ra{};
   ra.bases = pk.bases.p;
   ra.hq = pk.hq.p;
@@ -517,9 +521,13 @@ static int count_owned(kh_ctx* ctx, Packed& pk, const kh_params& p, hipStream_t 
   ra.shards = shards;
   ra.owner = p.owner;
   ra.p1 = (uint32_t)p1;
+  ra.win = win.p;
+  ra.lx = lx.p;
+  ra.rx = rx.p;
   ra.h1 = h1.p;
   ra.ctr = ctr;
   mark(ctx, 2, s);
+  launch_own_planes(ra, s);
   launch_own_hist(ra, grid, s);
   exclusive_scan_u32(h1.p, (int64_t)nb1 * grid, part.p, s);
   launch_gather_strided(h1.p, (uint64_t)grid, (uint32_t)nb1, b1.p, s);

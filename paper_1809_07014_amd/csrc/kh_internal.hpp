@@ -196,6 +196,9 @@ struct OwnRouteArgs {
   const uint64_t* st;
   int64_t base_words, plane_words, n;
   uint32_t k, shards, owner, p1;
+  uint64_t* win;            // planes of this k by window start (k_own_planes),
+  uint64_t* lx;             // plane_words each: k-mer, left and right
+  uint64_t* rx;             // neighbour is an extension
   uint32_t* h1;             // (1 << p1) x grid matrix, bucket-major
   uint64_t* rec;            // emit: records, R words each
   unsigned long long* ctr;  // kCtrWindows
@@ -264,6 +267,7 @@ struct OwnCopyArgs {
 
 int own_chunk_records(uint32_t k);
 int own_slots(uint32_t k);
+void launch_own_planes(const OwnRouteArgs& a, hipStream_t s);
 void launch_own_hist(const OwnRouteArgs& a, int grid, hipStream_t s);
 void launch_own_emit(const OwnRouteArgs& a, int grid, hipStream_t s);
 void launch_own_part(const OwnPartArgs& a, uint32_t n_chunks, int scatter, hipStream_t s);

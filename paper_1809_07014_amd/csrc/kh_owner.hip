@@ -22,6 +22,8 @@
 // R = own_record_words(k) words, most significant first.  Owners count these
 // partial keys (they share the digit) and put the digit back when
 // they write their rows.
+#include <algorithm>
+
 #include "kh_internal.hpp"
 
 namespace kh {
@@ -79,59 +81,6 @@ __device__ __forceinline__ void load_record(const uint64_t* __restrict__ rec, ui
   }
 }
 
-// The canonical key and extension byte of the window at p (staged tile at
-// O) whose forward words f and reverse complement r are known; false if it
-// is not a k-mer or belongs to another key part.
-template <int W>
-__device__ __forceinline__ bool own_window_fr(const uint64_t* s_bases, const uint64_t* s_hq,
-                                              const uint64_t* s_bad, const uint64_t* s_st,
-                                              int64_t p, int64_t O, int64_t n_end, uint32_t k,
-                                              uint32_t shards, uint32_t owner,
-                                              const uint64_t (&f)[W], const uint64_t (&r)[W],
-                                              uint64_t (&key)[W], uint32_t& e6,
-                                              int lbase = -1, int rbase = -1) {
-  if (p + (int64_t)k > n_end) return false;
-  const uint32_t lp = (uint32_t)(p - O);
-  if (any_bits(s_bad, lp, k) || any_bits(s_st, lp + 1, k - 1)) return false;
-  const bool use_rc = words_less<W>(r, f);
-#pragma unroll
-  for (int w = 0; w < W; ++w) key[w] = use_rc ? r[w] : f[w];
-  if (shards > 1 && owner_of<W>(key, shards) != owner) return false;
-  // the neighbouring bases (the caller's, when it has them: lbase, rbase)
-  int l = -1, rr = -1;
-  if (!get_bit(s_st, lp) && get_bit(s_hq, lp - 1))
-    l = lbase >= 0 ? lbase : (int)get_base(s_bases, lp - 1);
-  if (p + (int64_t)k < n_end && !get_bit(s_st, lp + k) && get_bit(s_hq, lp + k))
-    rr = rbase >= 0 ? rbase : (int)get_base(s_bases, lp + k);
-  int L = l, Rt = rr;
-  if (use_rc) {
-    L = rr >= 0 ? 3 - rr : -1;
-    Rt = l >= 0 ? 3 - l : -1;
-  }
-  e6 = (L >= 0 ? 32u | ((uint32_t)L << 3) : 0u) | (Rt >= 0 ? 4u | (uint32_t)Rt : 0u);
-  return true;
-}
-
-// A window of the staged tile as its canonical key and extension byte
-// (Section II-B: every k-mer of a read, its neighbours as extensions when
-// they pass the quality cutoff; on the reverse strand the sides swap and
-// complement).  False if it is not a k-mer or belongs to another key part.
-template <int W>
-__device__ __forceinline__ bool own_window(const uint64_t* s_bases, const uint64_t* s_hq,
-                                           const uint64_t* s_bad, const uint64_t* s_st,
-                                           int64_t p, int64_t O, int64_t n_end, uint32_t k,
-                                           uint32_t shards, uint32_t owner,
-                                           uint64_t (&key)[W], uint32_t& e6) {
-  if (p + (int64_t)k > n_end) return false;
-  const uint32_t lp = (uint32_t)(p - O);
-  if (any_bits(s_bad, lp, k) || any_bits(s_st, lp + 1, k - 1)) return false;
-  uint64_t f[W], r[W];
-  window_words<W>(s_bases, 2 * lp, k, f);
-  revcomp_words<W>(f, k, r);
-  return own_window_fr<W>(s_bases, s_hq, s_bad, s_st, p, O, n_end, k, shards, owner, f, r, key,
-                          e6);
-}
-
 // The next window's words: base b enters at the right of the forward words
 // and, complemented, at the left of the reverse complement (k-base values,
 // W words most significant first, the top word holding 2k - 64 (W - 1) bits).
@@ -146,27 +95,6 @@ __device__ __forceinline__ void roll_words(uint64_t (&f)[W], uint64_t (&r)[W], u
 #pragma unroll
   for (int j = W - 1; j > 0; --j) r[j] = (r[j] >> 2) | (r[j - 1] << 62);
   r[0] = (r[0] >> 2) | ((uint64_t)(3u - b) << (tb - 2));
-}
-
-// Level-1 bucket of the window at p without forming its key: the top p1
-// bits of the canonical key are the smaller of the window's first p1 / 2
-// bases and the reverse complement of its last p1 / 2 bases (when the two
-// are equal, the key starts with them whichever strand it is read on).
-// -1 if the window is not a k-mer.
-__device__ __forceinline__ int own_top(const uint64_t* s_bases, const uint64_t* s_bad,
-                                       const uint64_t* s_st, int64_t p, int64_t O,
-                                       int64_t n_end, uint32_t k, int p1) {
-  if (p + (int64_t)k > n_end) return -1;
-  const uint32_t lp = (uint32_t)(p - O);
-  if (any_bits(s_bad, lp, k) || any_bits(s_st, lp + 1, k - 1)) return -1;
-  const uint32_t nb = (uint32_t)p1 >> 1;
-  const uint32_t f = (uint32_t)get_bits(s_bases, 2 * lp, (uint32_t)p1);
-  const uint32_t t = (uint32_t)get_bits(s_bases, 2 * (lp + k - nb), (uint32_t)p1);
-  // reverse the order of t's bases: reverse its bits, then swap each pair back
-  uint32_t r = __builtin_bitreverse32(t) >> (32 - p1);
-  r = ((r >> 1) & 0x55555555u) | ((r & 0x55555555u) << 1);
-  r = ~r & ((1u << p1) - 1u);  // complement
-  return (int)(f < r ? f : r);
 }
 
 // Records of a batch starting at record b0 that lane `tid` holds (records
@@ -240,75 +168,161 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t x, uint32_t& excl,
 
 // ------------------------------------------------------ level 1 route ----
 
-// Routing tiles: kOwnTiles tiles of window starts staged at once, one
-// window of each tile per lane.
-constexpr int kOwnTiles = kOwnRouteThreads * 4 / kTile;
-constexpr int kOwnSpan = kOwnTiles * kTile + 256;  // staged positions (k <= 127)
-constexpr int kOwnBaseWords = kOwnSpan / 32 + 1;
-constexpr int kOwnPlaneWords = kOwnSpan / 64 + 1;
-constexpr int kOwnTile = kOwnTiles * kTile;        // window starts per routing tile
+// x << s over three words, most significant first, 0 <= s < 64.
+__device__ __forceinline__ void shl3(const uint64_t (&x)[3], int s, uint64_t (&y)[3]) {
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+    y[i] = s == 0 ? x[i] : (x[i] << s) | (i < 2 ? x[i + 1] >> (64 - s) : 0ull);
+}
 
-// Stage the planes of positions [O, O + kOwnSpan) (as stage_tile: outside the
-// read set no bases, every position bad).
-__device__ __forceinline__ void stage_tile_any(const OwnRouteArgs& a, int64_t O,
-                                               uint64_t* s_bases, uint64_t* s_hq,
-                                               uint64_t* s_bad, uint64_t* s_st) {
-  for (int i = threadIdx.x; i < kOwnBaseWords; i += blockDim.x) {
-    const int64_t gw = O / 32 + i;
-    s_bases[i] = (gw >= 0 && gw < a.base_words) ? a.bases[gw] : 0ull;
+// The windows of one k as three bit planes indexed by window start, 64 starts
+// per thread: win (it is a k-mer: no non-base in [p, p + k), no read start in
+// (p, p + k)), lx (its left neighbour is an extension: p starts no read and
+// base p - 1 is of high quality) and rx (likewise base p + k).  A run of k - 1
+// set-or-not bits is a shifted OR doubled log2(k) times, so 64 windows cost
+// what one costs when each looks at its own k bits; the routing passes then
+// read one bit per window and plane.  Positions from n on are marked as
+// non-bases, so windows that end past n are none.
+//
+// Bound by the planes: 3/8 byte in and 3/8 out per base; 1.5e9 bases 0.30 ms.
+__global__ __launch_bounds__(kBlock) void k_own_planes(OwnRouteArgs a) {
+  const int64_t w = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (w >= (a.n + 63) / 64) return;
+  const int k = (int)a.k;
+  uint64_t c[3], t[3];
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+    c[i] = w + i < a.plane_words ? a.bad[w + i] | a.st[w + i] : ~0ull;
+  uint64_t x[3] = {0, 0, 0};
+  if (k > 1) {  // any of the next k - 1 positions
+    shl3(c, 1, x);
+    int m = 1;
+    while (2 * m <= k - 1) {
+      shl3(x, m, t);
+#pragma unroll
+      for (int i = 0; i < 3; ++i) x[i] |= t[i];
+      m *= 2;
+    }
+    shl3(x, k - 1 - m, t);
+    x[0] |= t[0];
   }
-  for (int i = threadIdx.x; i < kOwnPlaneWords; i += blockDim.x) {
-    const int64_t gw = O / 64 + i;
-    const bool in = gw >= 0 && gw < a.plane_words;
-    s_hq[i] = in ? a.hq[gw] : 0ull;
-    s_bad[i] = in ? a.bad[gw] : ~0ull;
-    s_st[i] = in ? a.st[gw] : 0ull;
+  a.win[w] = ~(a.bad[w] | x[0]);
+  a.lx[w] = ((a.hq[w] >> 1) | (w > 0 ? a.hq[w - 1] << 63 : 0ull)) & ~a.st[w];
+  uint64_t y[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int64_t g = w + (k >> 6) + i;
+    y[i] = g < a.plane_words ? a.hq[g] & ~a.st[g] : 0ull;
+  }
+  const int s = k & 63;  // k is odd: 1 .. 63
+  a.rx[w] = (y[0] << s) | (y[1] >> (64 - s));
+}
+
+// h mod d with inv = floor((2^64 - 1) / d): the estimate of the quotient is
+// at most one (two for the inverse's own rounding) short.
+__device__ __forceinline__ uint32_t mod_u32(uint64_t h, uint32_t d, uint64_t inv) {
+  uint64_t r = h - __umul64hi(h, inv) * d;
+  if (r >= d) r -= d;
+  if (r >= d) r -= d;
+  return (uint32_t)r;
+}
+
+// A key-space part (owner of shards): the windows of other parts leave the
+// win plane, four consecutive windows a thread, so that the histogram and the
+// emit route only the part's own and no key is hashed twice.
+//
+// Bound by forming and hashing every window's key (VALU).  5.6e8 windows of
+// k = 77, part 0 of 8: 2.4 ms, and histogram and emit 0.3 and 2.8 ms; when
+// both formed and hashed every key (with a 64-bit division) they took 7.0 and
+// 7.9 ms.
+template <int W>
+__global__ __launch_bounds__(kBlock) void k_own_part_filter(OwnRouteArgs a, uint64_t inv) {
+  const int64_t words = (a.n + 63) / 64;
+  for (int64_t g = (int64_t)blockIdx.x * kBlock + threadIdx.x; g < 16 * words;
+       g += (int64_t)gridDim.x * kBlock) {
+    const int64_t p0 = 4 * g, w = p0 >> 6;
+    const uint32_t v4 = (uint32_t)(a.win[w] >> (60 - (p0 & 63))) & 15u;
+    uint32_t keep = 0;
+    if (v4) {
+      uint64_t fw[W], rw[W];
+      window_words<W>(a.bases + (p0 >> 5), 2 * (uint32_t)(p0 & 31), a.k, fw);
+      revcomp_words<W>(fw, a.k, rw);
+      const int64_t q0 = p0 + a.k;
+      const uint32_t rb = (uint32_t)get_bits(a.bases + (q0 >> 5), 2 * (uint32_t)(q0 & 31), 8);
+#pragma unroll
+      for (int pw = 0; pw < 4; ++pw) {
+        if (pw > 0) roll_words<W>(fw, rw, (rb >> (8 - 2 * pw)) & 3u, a.k);
+        if (!((v4 >> (3 - pw)) & 1u)) continue;
+        const bool use_rc = words_less<W>(rw, fw);
+        uint64_t h = 0;
+#pragma unroll
+        for (int j = 0; j < W; ++j) h = splitmix_out(h ^ (use_rc ? rw[j] : fw[j]));
+        if (mod_u32(h, a.shards, inv) == a.owner) keep |= 8u >> pw;
+      }
+    }
+    uint64_t m = (uint64_t)keep << (60 - (p0 & 63));  // 16 lanes hold a word
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) m |= __shfl_xor((unsigned long long)m, o);
+    if ((threadIdx.x & 15) == 0) a.win[w] = m;
   }
 }
 
+// Routing tiles: kOwnTile consecutive window starts, four of them per lane.
+constexpr int kOwnLane = 4;
+constexpr int kOwnTile = kOwnRouteThreads * kOwnLane;
+
 // Level-1 histogram: block b counts the buckets of the windows of routing
 // tiles b, b + grid, ... (the tiles the emit kernel gives the same block)
-// into column b of the bucket-major matrix h1[bucket * grid + b].
-template <int W>
+// into column b of the bucket-major matrix h1[bucket * grid + b].  The top p1
+// bits of a canonical key are the smaller of the window's first p1 / 2 bases
+// and the reverse complement of its last p1 / 2 (when the two are equal, the
+// key starts with them whichever strand it is read on), so no key is formed:
+// a thread walks 32 consecutive windows and shifts one base into each of the
+// two digits.
+//
+// Bound by the LDS histogram's atomics and the base stream (3/8 byte per
+// window).  1.3e9 windows of k = 21: 0.85 ms (5.4 ms with every window's
+// digits and validity bits read from a staged tile).
+constexpr int kHistTile = kOwnTile / 32;                     // threads per routing tile
+constexpr int kHistTiles = kOwnRouteThreads / kHistTile;     // tiles a block takes at once
+
 __global__ __launch_bounds__(kOwnRouteThreads) void k_own_hist(OwnRouteArgs a) {
-  __shared__ uint64_t s_bases[kOwnBaseWords];
-  __shared__ uint64_t s_hq[kOwnPlaneWords];
-  __shared__ uint64_t s_bad[kOwnPlaneWords];
-  __shared__ uint64_t s_st[kOwnPlaneWords];
   __shared__ uint32_t s_h[kOwnL1Max];
   __shared__ uint64_t s_red[kOwnRouteThreads / 64];
   const int tid = threadIdx.x;
   const int nbins = 1 << a.p1;
   for (int i = tid; i < nbins; i += kOwnRouteThreads) s_h[i] = 0;
-  const int koff = 64 * W - 2 * (int)a.k;
+  lds_barrier();
   const int64_t n_tiles = (a.n + kOwnTile - 1) / kOwnTile;
+  const uint32_t p1 = a.p1, nb = p1 >> 1, dmask = (1u << p1) - 1u;
   uint64_t nwin = 0;
-  for (int64_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
-    const int64_t P0 = t * kOwnTile, O = P0 - kHalo;
-    lds_barrier();
-    stage_tile_any(a, O, s_bases, s_hq, s_bad, s_st);
-    lds_barrier();
-    if (a.shards > 1) {  // the part filter needs the whole key
-#pragma unroll 1
-      for (int j = 0; j < kOwnTile / kOwnRouteThreads; ++j) {
-        uint64_t key[W];
-        uint32_t e6;
-        if (own_window<W>(s_bases, s_hq, s_bad, s_st, P0 + j * kOwnRouteThreads + tid, O, a.n,
-                          a.k, a.shards, a.owner, key, e6)) {
-          ++nwin;
-          atomicAdd(&s_h[top_bits<W>(key, koff, a.p1)], 1u);
-        }
-      }
-    } else {
-#pragma unroll
-      for (int j = 0; j < kOwnTile / kOwnRouteThreads; ++j) {
-        const int b = own_top(s_bases, s_bad, s_st, P0 + j * kOwnRouteThreads + tid, O, a.n,
-                              a.k, (int)a.p1);
-        if (b >= 0) {
-          ++nwin;
-          atomicAdd(&s_h[b], 1u);
-        }
-      }
+  for (int64_t t = blockIdx.x + (int64_t)(tid / kHistTile) * gridDim.x; t < n_tiles;
+       t += (int64_t)kHistTiles * gridDim.x) {
+    const int64_t p0 = t * kOwnTile + 32 * (tid % kHistTile);
+    if (p0 >= a.n) continue;
+    const uint32_t v = (uint32_t)(a.win[p0 >> 6] >> (32 - (p0 & 63)));
+    if (!v) continue;
+    nwin += __popc(v);
+    // fx: the bases that enter the first digit, tx: those that enter the last
+    const int64_t q0 = p0 + nb - 1, e0 = p0 + a.k - 1;
+    const uint64_t* fb = a.bases + (q0 >> 5);
+    const uint64_t* tb = a.bases + (e0 >> 5);
+    const uint64_t fx = get_bits(fb, 2 * (uint32_t)(q0 & 31), 64);
+    const uint64_t tx = get_bits(tb, 2 * (uint32_t)(e0 & 31), 64);
+    uint32_t f = 0, r = 0;
+    if (nb > 1) {  // the first window's other nb - 1 bases
+      f = (uint32_t)(a.bases[p0 >> 5] >> (64 - 2 * (nb - 1)));
+      const int64_t l0 = e0 - (nb - 1);
+      const uint32_t l = (uint32_t)get_bits(a.bases + (l0 >> 5), 2 * (uint32_t)(l0 & 31),
+                                            2 * (nb - 1));
+      for (uint32_t j = 0; j < nb - 1; ++j)  // base j of l: place j + 1 from the low end
+        r |= (3u - ((l >> (2 * (nb - 2 - j))) & 3u)) << (2 * (j + 1));
+    }
+#pragma unroll 8
+    for (int i = 0; i < 32; ++i) {
+      f = ((f << 2) | ((uint32_t)(fx >> (62 - 2 * i)) & 3u)) & dmask;
+      r = (r >> 2) | ((3u - ((uint32_t)(tx >> (62 - 2 * i)) & 3u)) << (p1 - 2));
+      if ((v >> (31 - i)) & 1u) atomicAdd(&s_h[f < r ? f : r], 1u);
     }
   }
   lds_barrier();
@@ -317,99 +331,122 @@ __global__ __launch_bounds__(kOwnRouteThreads) void k_own_hist(OwnRouteArgs a) {
   block_add(&a.ctr[kCtrWindows], nwin, s_red);
 }
 
-// Level-1 emit, staged: the same routing tiles as k_own_hist, taken in
-// batches (two tiles for one-word records, else one); a batch's records are
-// ranked by bucket in LDS and leave as one contiguous run per bucket at the
-// block's cursors (the scanned matrix column), so that HBM sees whole lines
-// rather than scattered 8-byte stores.
+// Level-1 emit: the same routing tiles as k_own_hist, taken in batches (two
+// tiles for one-word records, else one).  A lane forms four consecutive
+// windows of a tile, the first one's words read from the staged bases, each
+// next one's by shifting one base in, and keeps their records; the bucket
+// counts' atomics return each record's rank in its bucket, so after a scan of
+// the counts the records go to LDS in bucket order and leave as one
+// contiguous run per bucket at the block's cursors (the scanned matrix
+// column): HBM sees whole lines rather than scattered 8-byte stores.
+//
+// One-word records are bound by the LDS exchange and its barriers at one block
+// per CU, longer ones more and more by their stores.  10M reads of 150 bases:
+// k = 21, 33, 55, 77, 99 take 7.6, 7.5, 10.2, 12.0 and 10.9 ms, from 14.1,
+// 15.7, 17.4, 19.0 and 19.4 ms when each window looked up its own validity and
+// extension bits and a record's bucket place was found by a second atomic.
 template <int R>
 struct EmitBatch {
-  static constexpr int kTiles = R == 1 ? 2 : 1;                  // routing tiles
-  static constexpr int kLane = kOwnTile / kOwnRouteThreads;       // windows per lane per tile
-  static constexpr int kCap = kTiles * kOwnTile;                  // records per batch
+  static constexpr int kTiles = R == 1 ? 2 : 1;       // routing tiles
+  static constexpr int kCap = kTiles * kOwnTile;      // records per batch
 };
+
+// Words staged per tile: its bases from 32 before it (the left neighbour of
+// its first window) to the right neighbour of its last (k <= 127), then 64
+// words of each plane.  One word per thread, loaded a tile ahead.
+constexpr int kOwnBaseWords = (32 + kOwnTile + 127 + kOwnLane + 31) / 32 + 1;
+constexpr int kOwnPlaneWords = kOwnTile / 64;
+constexpr int kOwnWin = kOwnBaseWords, kOwnLx = kOwnWin + kOwnPlaneWords,
+              kOwnRx = kOwnLx + kOwnPlaneWords, kOwnStaged = kOwnRx + kOwnPlaneWords;
+static_assert(kOwnStaged <= kOwnRouteThreads, "one staged word per thread");
+
+__device__ __forceinline__ uint64_t tile_word(const OwnRouteArgs& a, int64_t P0, int tid) {
+  if (tid < kOwnWin) {
+    const int64_t g = P0 / 32 - 1 + tid;
+    return g >= 0 && g < a.base_words ? a.bases[g] : 0ull;
+  }
+  if (tid >= kOwnStaged) return 0ull;
+  const uint64_t* plane = tid < kOwnLx ? a.win : tid < kOwnRx ? a.lx : a.rx;
+  const int64_t g = P0 / 64 + (tid - kOwnWin) % kOwnPlaneWords;
+  return g < (a.n + 63) / 64 ? plane[g] : 0ull;
+}
 
 template <int W, int R>
 __global__ __launch_bounds__(kOwnRouteThreads) void k_own_emit_staged(OwnRouteArgs a) {
   constexpr int BT = EmitBatch<R>::kTiles;
-  constexpr int PT = EmitBatch<R>::kLane;
+  constexpr int PT = kOwnLane;
   constexpr int CAP = EmitBatch<R>::kCap;
-  __shared__ uint64_t s_bases[kOwnBaseWords];
-  __shared__ uint64_t s_hq[kOwnPlaneWords];
-  __shared__ uint64_t s_bad[kOwnPlaneWords];
-  __shared__ uint64_t s_st[kOwnPlaneWords];
-  __shared__ uint64_t s_rec[CAP * R];  // records by window slot (unsorted)
-  __shared__ uint16_t s_binr[CAP];     // bucket of each window slot's record (~0: none)
-  __shared__ uint16_t s_inv[CAP];      // window slot of each bucket-ordered position
+  __shared__ uint64_t s_tile[kOwnStaged];
+  __shared__ uint64_t s_rec[CAP * R];  // the batch's records in bucket order
+  __shared__ uint16_t s_bin[CAP];      // and their buckets
   __shared__ uint32_t s_cnt[kOwnL1Max];
   __shared__ uint32_t s_start[kOwnL1Max];
-  __shared__ uint32_t s_cur[kOwnL1Max];
+  __shared__ uint32_t s_dst[kOwnL1Max];  // cursor minus place in the batch
   __shared__ uint32_t s_w[kOwnRouteThreads / 64];
   static_assert(kOwnL1Max <= kOwnRouteThreads, "one bucket per lane in the scan");
-  static_assert(CAP <= 65535, "window slots fit 16 bits");
   const int tid = threadIdx.x;
   const int nbins = 1 << a.p1;
-  const int roff = 64 * (W + 1) - 2 * (int)a.k - 6;  // the digit in a full record
   const int top_bits_kept = own_rest_bits(a.k) + 6 - 64 * (R - 1);  // 1..64
   const uint64_t top_mask = top_bits_kept >= 64 ? ~0ull : (1ull << top_bits_kept) - 1ull;
+  const int tb = 2 * (int)a.k - 64 * (W - 1);  // bits of the top word
   const int64_t G = gridDim.x, blk = blockIdx.x;
-  for (int i = tid; i < nbins; i += kOwnRouteThreads) {
-    s_cur[i] = a.h1[(uint64_t)i * G + blk];
-    s_cnt[i] = 0;
-  }
+  uint32_t cur = tid < nbins ? a.h1[(uint64_t)tid * G + blk] : 0u;  // this lane's bucket's
+  if (tid < nbins) s_cnt[tid] = 0;
   const int64_t n_tiles = (a.n + kOwnTile - 1) / kOwnTile;
   const int64_t mine = n_tiles > blk ? (n_tiles - blk + G - 1) / G : 0;  // tiles blk + j G
-  // The block's tile j is staged as soon as tile j - 1's windows are formed,
-  // before the batch's records are written out: one counter tracks a wave's
-  // loads and stores alike, so staging after the write-out would wait for
-  // every store of the batch to land.
-  if (mine > 0) stage_tile_any(a, blk * kOwnTile - kHalo, s_bases, s_hq, s_bad, s_st);
+  if (mine > 0 && tid < kOwnStaged) s_tile[tid] = tile_word(a, blk * kOwnTile, tid);
   lds_barrier();
   for (int64_t j0 = 0; j0 < mine; j0 += BT) {
+    uint64_t v[BT * PT][R];
+    uint32_t br[BT * PT];  // bucket << 16 | rank, ~0 for no record
+#pragma unroll
     for (int bt = 0; bt < BT; ++bt) {
-      const bool has = j0 + bt < mine;  // uniform over the block
-      const int64_t P0 = (blk + (j0 + bt) * G) * kOwnTile, O = P0 - kHalo;
-      // a lane's PT consecutive windows, one at a time (its record goes to
-      // LDS at once): the first one's words are read from the tile, each
-      // next one's shift one base in; the bases shifted in and out are also
-      // the windows' neighbours
-      const int64_t p0 = P0 + (int64_t)tid * PT;
-      const uint32_t lp0 = (uint32_t)(p0 - O);
-      const int tb = 2 * (int)a.k - 64 * (W - 1);  // bits of the top word
+      // the next tile's word: in flight while this one's windows are formed
+      const int64_t jn = j0 + bt + 1;
+      const uint64_t next = jn < mine ? tile_word(a, (blk + jn * G) * kOwnTile, tid) : 0ull;
+      const uint32_t at = 4 * (uint32_t)tid;  // the lane's first window in the tile
+      const int sh = 60 - (int)(at & 63);
+      const uint32_t v4 =
+          j0 + bt < mine ? (uint32_t)(s_tile[kOwnWin + (at >> 6)] >> sh) & 15u : 0u;
+      const uint32_t l4 = (uint32_t)(s_tile[kOwnLx + (at >> 6)] >> sh) & 15u;
+      const uint32_t r4 = (uint32_t)(s_tile[kOwnRx + (at >> 6)] >> sh) & 15u;
+      const uint32_t lp = 32 + at;  // staged base of that window
       uint64_t fw[W], rw[W];
-      window_words<W>(s_bases, 2 * lp0, a.k, fw);
+      window_words<W>(s_tile, 2 * lp, a.k, fw);
       revcomp_words<W>(fw, a.k, rw);
-      uint32_t left = get_base(s_bases, lp0 - 1), right = 0;
-#pragma unroll 1
+      const uint32_t rb = (uint32_t)get_bits(s_tile, 2 * (lp + a.k), 8);  // right neighbours
+      uint32_t left = get_base(s_tile, lp - 1);
+#pragma unroll
       for (int pw = 0; pw < PT; ++pw) {
-        const int slot = (bt * PT + pw) * kOwnRouteThreads + tid;
+        const int q = bt * PT + pw;
         if (pw > 0) {
           left = (uint32_t)(fw[0] >> (tb - 2)) & 3u;  // the base leaving the window
-          roll_words<W>(fw, rw, right, a.k);
+          roll_words<W>(fw, rw, (rb >> (8 - 2 * pw)) & 3u, a.k);
         }
-        right = get_base(s_bases, lp0 + pw + a.k);  // staged: lp0 + 3 + 127 < kOwnSpan
-        uint64_t key[W];
-        uint32_t e6 = 0;
-        uint16_t b16 = 0xffffu;
-        if (has && own_window_fr<W>(s_bases, s_hq, s_bad, s_st, p0 + pw, O, a.n, a.k, a.shards,
-                                    a.owner, fw, rw, key, e6, (int)left, (int)right)) {
-          uint64_t f[W + 1];
-          make_record<W, W + 1>(key, e6, f);
-          const uint32_t b = top_bits<W + 1>(f, roff, a.p1);
-          // the low R words, without the digit's bits
+        const uint32_t right = (rb >> (6 - 2 * pw)) & 3u;
+        const uint32_t lb = (l4 >> (3 - pw)) & 1u, xb = (r4 >> (3 - pw)) & 1u;
+        const bool use_rc = words_less<W>(rw, fw);
+        // extension byte: valid bit and base per side; on the reverse strand
+        // the sides swap and complement
+        const uint32_t e_l = lb ? 4u | left : 0u, e_r = xb ? 4u | right : 0u;
+        const uint32_t c_l = xb ? 7u - right : 0u, c_r = lb ? 7u - left : 0u;
+        const uint32_t e6 = use_rc ? (c_l << 3) | c_r : (e_l << 3) | e_r;
+        uint64_t key[W], f[W + 1];
 #pragma unroll
-          for (int w = 0; w < R; ++w)
-            s_rec[slot * R + w] = w == 0 ? f[W + 1 - R] & top_mask : f[W + 1 - R + w];
-          atomicAdd(&s_cnt[b], 1u);
-          b16 = (uint16_t)b;
-        }
-        s_binr[slot] = b16;
+        for (int w = 0; w < W; ++w) key[w] = use_rc ? rw[w] : fw[w];
+        const int p1 = (int)a.p1;
+        const uint32_t b =
+            tb >= p1 ? (uint32_t)(key[0] >> (tb - p1))
+                     : (uint32_t)((key[0] << (p1 - tb)) | (key[W > 1 ? 1 : 0] >> (64 - p1 + tb)));
+        make_record<W, W + 1>(key, e6, f);
+        // the low R words, without the digit's bits
+#pragma unroll
+        for (int w = 0; w < R; ++w) v[q][w] = w == 0 ? f[W + 1 - R] & top_mask : f[W + 1 - R + w];
+        br[q] = ~0u;
+        if ((v4 >> (3 - pw)) & 1u) br[q] = (b << 16) | atomicAdd(&s_cnt[b], 1u);
       }
       lds_barrier();  // every window of the staged tile is formed
-      if (j0 + bt + 1 < mine) {
-        const int64_t P1 = (blk + (j0 + bt + 1) * G) * kOwnTile;
-        stage_tile_any(a, P1 - kHalo, s_bases, s_hq, s_bad, s_st);
-      }
+      if (tid < kOwnStaged) s_tile[tid] = next;
       if (bt + 1 < BT) lds_barrier();  // the batch's next tile is formed next
     }
     uint32_t excl = 0;
@@ -417,26 +454,26 @@ __global__ __launch_bounds__(kOwnRouteThreads) void k_own_emit_staged(OwnRouteAr
     const uint32_t total = block_excl_scan(c, excl, s_w);
     if (tid < nbins) {
       s_start[tid] = excl;
-      s_cnt[tid] = 0;  // now the fill count of each bucket
+      s_dst[tid] = cur - excl;
+      s_cnt[tid] = 0;
+      cur += c;
     }
     lds_barrier();
-    for (int q = 0; q < BT * PT; ++q) {  // bucket-ordered positions of the records
-      const int slot = q * kOwnRouteThreads + tid;
-      const uint32_t b = s_binr[slot];
-      if (b != 0xffffu) s_inv[s_start[b] + atomicAdd(&s_cnt[b], 1u)] = (uint16_t)slot;
+#pragma unroll
+    for (int q = 0; q < BT * PT; ++q) {
+      if (br[q] == ~0u) continue;
+      const uint32_t b = br[q] >> 16, pos = s_start[b] + (br[q] & 0xffffu);
+#pragma unroll
+      for (int w = 0; w < R; ++w) s_rec[pos * R + w] = v[q][w];
+      s_bin[pos] = (uint16_t)b;
     }
     lds_barrier();
     for (uint32_t i = tid; i < total * R; i += kOwnRouteThreads) {
-      const uint32_t rr = i / R, w = i - rr * R;
-      const uint32_t src = s_inv[rr], b = s_binr[src];
-      a.rec[((uint64_t)s_cur[b] + (rr - s_start[b])) * R + w] = s_rec[src * R + w];
+      const uint32_t rr = i / R;
+      a.rec[(uint64_t)(s_dst[s_bin[rr]] + rr) * R + (i - rr * R)] = s_rec[i];
     }
-    lds_barrier();
-    if (tid < nbins) {
-      s_cur[tid] += c;
-      s_cnt[tid] = 0;
-    }
-    lds_barrier();  // the next batch counts into s_cnt at once
+    // the next batch writes these arrays only behind its own barriers, which
+    // this wave reaches after its write-out
   }
 }
 
@@ -1093,14 +1130,25 @@ void launch_gather_strided(const uint32_t* src, uint64_t stride, uint32_t n, uin
                      src, stride, n, dst);
 }
 
-void launch_own_hist(const OwnRouteArgs& a, int grid, hipStream_t s) {
-  const dim3 g(grid), t(kOwnRouteThreads);
+void launch_own_planes(const OwnRouteArgs& a, hipStream_t s) {
+  const int64_t words = (a.n + 63) / 64;
+  hipLaunchKernelGGL(k_own_planes, dim3((unsigned)((words + kBlock - 1) / kBlock)), dim3(kBlock),
+                     0, s, a);
+  if (a.shards <= 1) return;
+  // a launch holds under 2^32 threads, which 4 windows a thread would pass
+  const dim3 g((unsigned)std::min<int64_t>((words * 16 + kBlock - 1) / kBlock, 1 << 20)),
+      t(kBlock);
+  const uint64_t inv = ~0ull / a.shards;
   switch ((a.k + 31) / 32) {
-    case 1: hipLaunchKernelGGL(k_own_hist<1>, g, t, 0, s, a); break;
-    case 2: hipLaunchKernelGGL(k_own_hist<2>, g, t, 0, s, a); break;
-    case 3: hipLaunchKernelGGL(k_own_hist<3>, g, t, 0, s, a); break;
-    default: hipLaunchKernelGGL(k_own_hist<4>, g, t, 0, s, a); break;
+    case 1: hipLaunchKernelGGL(k_own_part_filter<1>, g, t, 0, s, a, inv); break;
+    case 2: hipLaunchKernelGGL(k_own_part_filter<2>, g, t, 0, s, a, inv); break;
+    case 3: hipLaunchKernelGGL(k_own_part_filter<3>, g, t, 0, s, a, inv); break;
+    default: hipLaunchKernelGGL(k_own_part_filter<4>, g, t, 0, s, a, inv); break;
   }
+}
+
+void launch_own_hist(const OwnRouteArgs& a, int grid, hipStream_t s) {
+  hipLaunchKernelGGL(k_own_hist, dim3(grid), dim3(kOwnRouteThreads), 0, s, a);
 }
 
 void launch_own_emit(const OwnRouteArgs& a, int grid, hipStream_t s) {
