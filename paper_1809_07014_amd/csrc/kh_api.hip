@@ -572,12 +572,16 @@ static int count_owned(kh_ctx* ctx, Packed& pk, const kh_params& p, hipStream_t 
   uint32_t slots = (uint32_t)T;
   if (const char* e = std::getenv("KMERHIP_OWNER_SLOTS"))
     slots = (uint32_t)std::max<long long>(16, std::min<long long>(T, std::atoll(e)));
-  // Records per owner: with the Bloom screen an owner's table only takes
-  // keys seen at least twice, so 2 x slots records always fit (false
-  // positives aside); without it, every record may be a new key.  An owner
-  // larger than that (a bucket already split by kOwnL2Max bits) may not fit:
-  // then every owner is split by two more bits and counted again.
-  double target = (p.use_bloom ? 2.0 : 1.0) * T;
+  // Owners of up to n_small records always fit (k_own_count).  Larger ones
+  // (a bucket already split by kOwnL2Max bits, or a prefix its bucket's others
+  // are rare beside) take the batched kernel, whose table may be too small for
+  // their keys: then every owner is split by two more bits and counted again.
+  // Owners are planned for 0.8 of n_small on average, since the prefixes of
+  // one bucket are not equally frequent: 10M reads at k = 21 .. 99 leave 3 to
+  // 4 % of the owners over it.
+  const uint32_t planned = (uint32_t)own_small_records(k) / (p.min_count >= 2 ? 1 : 2);
+  const uint32_t n_small = slots < (uint32_t)T ? 0u : planned;
+  double target = 0.8 * planned;
   const int p2max = std::max(0, std::min(kOwnL2Max, 2 * (int)k - p1));
   for (int attempt = 0;; ++attempt) {
     // the previous attempt staged its rows over the level-1 records
@@ -600,7 +604,7 @@ static int count_owned(kh_ctx* ctx, Packed& pk, const kh_params& p, hipStream_t 
       m_size += (uint64_t)x.chunks << p2;
     }
     Buf<OwnBucket> dbk(pool);
-    Buf<uint32_t> m(pool), start2(pool), rows_sb(pool), row_off(pool), part2(pool);
+    Buf<uint32_t> m(pool), start2(pool), rows_sb(pool), row_off(pool), part2(pool), big(pool);
     Buf<unsigned long long> stripes(pool);
     Buf<uint16_t> owner_bucket(pool), chunk_bucket(pool);
     Buf<uint8_t> owner_pfx(pool);
@@ -610,6 +614,7 @@ static int count_owned(kh_ctx* ctx, Packed& pk, const kh_params& p, hipStream_t 
     KH_TRY(dbk.alloc(nb1));
     KH_TRY(m.alloc(std::max<uint64_t>(m_size, 1)));
     KH_TRY(start2.alloc(n_owners + 1));
+    KH_TRY(big.alloc(2 * (n_owners / 2 + 1) + 2));  // the list, then its length
     KH_TRY(rows_sb.alloc(n_owners));
     KH_TRY(row_off.alloc(n_owners));
     KH_TRY(part2.alloc(scan_tmp_words((int64_t)n_owners + 1)));
@@ -625,8 +630,12 @@ static int count_owned(kh_ctx* ctx, Packed& pk, const kh_params& p, hipStream_t 
     pa.owner_bucket = owner_bucket.p;
     pa.owner_pfx = owner_pfx.p;
     pa.chunk_bucket = chunk_bucket.p;
+    pa.big = big.p;
+    pa.n_big = big.p + 2 * (n_owners / 2 + 1);
+    pa.n_small = n_small;
     pa.k = k;
     pa.p1 = (uint32_t)p1;
+    launch_fill_u64(reinterpret_cast<uint64_t*>(pa.n_big), 1, 0ull, s);
     launch_own_maps(pa, s);
     launch_own_part(pa, (uint32_t)n_chunks, 0, s);
     launch_own_colscan(pa, (uint32_t)n_owners, s);
@@ -640,8 +649,8 @@ static int count_owned(kh_ctx* ctx, Packed& pk, const kh_params& p, hipStream_t 
     // records at any useful coverage), blocks taking chunks of it in turn;
     // if it runs out, the pass runs again with staging of exactly the rows,
     // every owner's at its scanned offset.
-    const uint32_t blocks =
-        (uint32_t)std::min<uint64_t>(n_owners, (uint64_t)ctx->cus * kOwnBlocksPerCU);
+    const uint32_t blocks = (uint32_t)std::min<uint64_t>(n_owners, 2ull * ctx->cus);
+    const bool any_big = *std::max_element(nbk.begin(), nbk.end()) > n_small;
     const uint64_t rb = 8ull * W + 4 + 32 + 2;  // key words, count, tallies, codes
     Buf<uint64_t> st_off(pool);
     Buf<uint32_t> st_fixed(pool);
@@ -665,7 +674,7 @@ static int count_owned(kh_ctx* ctx, Packed& pk, const kh_params& p, hipStream_t 
       // every key is a row, and rows take more bytes than records: stage
       // them in a buffer of their own, sized for a row per window plus what
       // the blocks' partly filled staging chunks leave unused
-      st_big_bytes = (n_rec + n_rec / 8 + 20ull * blocks * (uint64_t)T) * rb + 512;
+      st_big_bytes = (n_rec + n_rec / 8 + 20ull * blocks * (uint64_t)own_small_records(k)) * rb + 512;
       KH_TRY(st_big.alloc(st_big_bytes));
       stage_in(st_big.p, st_big_bytes);
     } else {
@@ -683,6 +692,9 @@ static int count_owned(kh_ctx* ctx, Packed& pk, const kh_params& p, hipStream_t 
     ca.err_ppm = p.err_ppm;
     ca.use_bloom = p.use_bloom ? 1u : 0u;
     ca.slots = slots;
+    ca.n_small = n_small;
+    ca.big = pa.big;
+    ca.n_big = pa.n_big;
     ca.st_off = st_off.p;
     ca.st_cursor = stripes.p + (size_t)kOwnStripes * kCtrCount;
     ca.rows_sb = rows_sb.p;
@@ -699,7 +711,7 @@ static int count_owned(kh_ctx* ctx, Packed& pk, const kh_params& p, hipStream_t 
       launch_fill_u64(reinterpret_cast<uint64_t*>(stripes.p),
                       (uint64_t)kOwnStripes * kCtrCount + 1, 0ull, s);
       if (dbg) launch_fill_u64(reinterpret_cast<uint64_t*>(prof.p), 8, 0ull, s);
-      launch_own_count(ca, blocks, s);
+      launch_own_count(ca, (uint32_t)ctx->cus, any_big, s);
       HIP_TRY(hipGetLastError());
       std::vector<uint64_t> hs((size_t)kOwnStripes * kCtrCount);
       HIP_TRY(hipMemcpyAsync(hs.data(), stripes.p, hs.size() * 8, hipMemcpyDeviceToHost, s));
@@ -743,11 +755,13 @@ static int count_owned(kh_ctx* ctx, Packed& pk, const kh_params& p, hipStream_t 
     ctx->last_stats[9] += c[kCtrHeavy];
     ctx->last_stats[11] = c[kCtrWindows];
     if (std::getenv("KMERHIP_OWNER_DEBUG"))
+{ uint32_t nb = 0; (void)hipMemcpy(&nb, pa.n_big, 4, hipMemcpyDeviceToHost);
+      std::fprintf(stderr, "owner k=%u: %u owners over %u records\n", k, nb, n_small);
       std::fprintf(stderr, "owner k=%u attempt %d: owners %llu chunks %llu matrix %llu, "
                    "%llu did not fit, largest %llu keys (slots %u), target %.0f records\n",
                    k, attempt, (unsigned long long)n_owners, (unsigned long long)n_chunks,
                    (unsigned long long)m_size, (unsigned long long)c[kCtrHeavy],
-                   (unsigned long long)c[kCtrWindows], slots, target);
+                   (unsigned long long)c[kCtrWindows], slots, target); }
     if (c[kCtrStatus] & kStatusProbeLimit) {
       if (attempt >= 2) {
         *unfit = true;

@@ -223,6 +223,9 @@ struct OwnPartArgs {
   uint16_t* owner_bucket;  // bucket of each owner (k_own_maps)
   uint8_t* owner_pfx;      // key bits an owner's keys share (p1 + its bucket's p2)
   uint16_t* chunk_bucket;  // bucket of each level-2 chunk
+  uint32_t* big;           // owners of more than n_small records (k_own_colscan)
+  uint32_t* n_big;         // their number (zero before)
+  uint32_t n_small;
   uint32_t k, p1;
 };
 
@@ -232,7 +235,10 @@ struct OwnCountArgs {
   const uint16_t* owner_bucket;  // level-1 bucket (top key bits) of each owner
   uint32_t n_owners;
   uint32_t k, p1, min_count, t_min_ext, t_base, err_ppm, use_bloom;
-  uint32_t slots;          // table slots used (<= own_slots(k); a testing hook)
+  uint32_t slots;          // a big owner's table slots (<= own_slots(k); a testing hook)
+  uint32_t n_small;        // owners of more records are the big ones, listed
+  const uint32_t* big;     //   in big
+  const uint32_t* n_big;
   uint64_t* st_keys;       // st_cap staging rows
   uint32_t* st_counts;
   uint32_t* st_ext;
@@ -267,14 +273,15 @@ struct OwnCopyArgs {
 
 int own_chunk_records(uint32_t k);
 int own_slots(uint32_t k);
+int own_small_records(uint32_t k);  // records of an owner that k_own_count holds
 void launch_own_planes(const OwnRouteArgs& a, hipStream_t s);
 void launch_own_hist(const OwnRouteArgs& a, int grid, hipStream_t s);
 void launch_own_emit(const OwnRouteArgs& a, int grid, hipStream_t s);
 void launch_own_part(const OwnPartArgs& a, uint32_t n_chunks, int scatter, hipStream_t s);
 void launch_own_maps(const OwnPartArgs& a, hipStream_t s);
 void launch_own_colscan(const OwnPartArgs& a, uint32_t n_owners, hipStream_t s);
-// blocks: persistent blocks (at most one per owner), one per compute unit
-void launch_own_count(const OwnCountArgs& a, uint32_t blocks, hipStream_t s);
+// Small owners, then (any_big) the listed big ones, in persistent blocks
+void launch_own_count(const OwnCountArgs& a, uint32_t cus, bool any_big, hipStream_t s);
 void launch_own_copy(const OwnCopyArgs& a, uint32_t n_owners, hipStream_t s);
 void launch_gather_strided(const uint32_t* src, uint64_t stride, uint32_t n, uint32_t* dst,
                            hipStream_t s);

@@ -605,7 +605,8 @@ __global__ __launch_bounds__(kOwnPartThreads) void k_own_scatter2(OwnPartArgs a)
 // d) turns its column (chunks 0, 1, ... of b) into exclusive prefixes and
 // leaves the owner's record count in tot[owner]; thread n_owners writes 0, so
 // that an exclusive scan of tot[0 .. n_owners] gives every owner's first
-// record and the total after the last.
+// record and the total after the last.  Owners of more than n_small records
+// are listed in big.
 __global__ void k_own_colscan(OwnPartArgs a, uint32_t n_owners) {
   const uint32_t sb = blockIdx.x * blockDim.x + threadIdx.x;
   if (sb > n_owners) return;
@@ -624,6 +625,7 @@ __global__ void k_own_colscan(OwnPartArgs a, uint32_t n_owners) {
     run += v;
   }
   a.start2[sb] = run;
+  if (run > a.n_small) a.big[atomicAdd(a.n_big, 1u)] = sb;
 }
 
 // ------------------------------------------------------------- owners ----
@@ -655,11 +657,13 @@ int own_slots(uint32_t k) {
   }
 }
 
-// One owner per block: Bloom pass A and count pass B over the owner's
-// records in LDS, then classify (count >= min_count, extension codes), sort
-// by key and write the rows to the owner's staging rows.
+// The owners with more records than k_own_count holds at once (a.big: key
+// prefixes shared by very many windows, down to the finest split): Bloom pass
+// A and count pass B over the records in batches, 32-bit tallies in an
+// open-addressing table of the keys that pass the screen, then classify
+// (count >= min_count, extension codes) and write the rows to staging.
 template <int R, int C>
-__global__ __launch_bounds__(kOwnThreads, kOwnThreads * kOwnBlocksPerCU / 256) void k_own_count(OwnCountArgs a) {
+__global__ __launch_bounds__(kOwnThreads, kOwnThreads * kOwnBlocksPerCU / 256) void k_own_count_big(OwnCountArgs a) {
   constexpr int T = OwnerShape<C>::kSlots;
   // records per lane per batch: an owner of the usual size (up to 2 T
   // records) is one batch
@@ -679,7 +683,7 @@ __global__ __launch_bounds__(kOwnThreads, kOwnThreads * kOwnBlocksPerCU / 256) v
   constexpr int ws = C;  // the launcher picks C = own_chunks(k)
   const int W = (int)(k + 31) / 32;
   const uint32_t tcap = a.slots < (uint32_t)T ? a.slots : (uint32_t)T;
-  const uint32_t N = a.n_owners, G = gridDim.x;
+  const uint32_t N = *a.n_big, G = gridDim.x;
   // optional phase clocks (thread 0, summed over the block's owners)
   uint64_t prof_acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   uint64_t prof_t = 0;
@@ -690,9 +694,10 @@ __global__ __launch_bounds__(kOwnThreads, kOwnThreads * kOwnBlocksPerCU / 256) v
     prof_t = now_;                                           \
   }
 
-  // Persistent blocks: owners sb = blockIdx.x, + G, ...
+  // Persistent blocks: the listed owners blockIdx.x, + G, ...
   uint64_t st_cur = 0, st_end = 0;  // the block's staging chunk (uniform)
-  for (uint32_t sb = blockIdx.x; sb < N; sb += G) {
+  for (uint32_t x = blockIdx.x; x < N; x += G) {
+  const uint32_t sb = a.big[x];
   const uint64_t r0 = a.start2[sb], r1 = a.start2[sb + 1];
   // an owner of at most NB records per lane is loaded once for both passes
   const bool one_batch = r1 - r0 <= kBatch;
@@ -1013,6 +1018,334 @@ __global__ __launch_bounds__(kOwnThreads, kOwnThreads * kOwnBlocksPerCU / 256) v
 #undef PROF_MARK
 }
 
+// Owners of up to kRecs records, counted without a filter and without key
+// slots: the records lie in LDS, a hash table of kSlots 32-bit words names for
+// every key its first record (index + 1 in the low half, 0: free) and counts
+// its occurrences (high half), and only the keys that become rows get tallies,
+// once their number is known, over the records' space.  An owner always fits:
+// there are more slots than records, and room for half as many rows (rows of
+// one record, min_count 1, come from owners of half the records).
+//
+// The tallies are 16 bits wide (an owner has under 2^16 records), two to a
+// word: 16 bytes a row.
+//
+// Two blocks of 512 threads share a CU's LDS, so that one block's barriers and
+// loads hide behind the other's work; as many records as that leaves room for
+// keep the level-2 runs long.
+//
+// Bound by instruction issue (about 140 vector instructions per 64 records),
+// then by the records and rows: 10M reads of 150 bases at k = 21, 33, 55, 77,
+// 99 take 8.9, 8.9, 8.8, 9.0 and 7.7 ms and the big owners (3 % of them) 1.1
+// ms each, from 18.8, 18.8, 18.6, 17.6 and 15.6 ms with a Bloom filter, key
+// slots and 32-bit tallies in one block's LDS per CU.  Probing for a group of
+// a lane's records at once instead of one after another is slower (11.0 ms at
+// k = 21): it issues more instructions.
+template <int R>
+struct SmallShape {
+  static constexpr int kThreads = 512;
+  static constexpr int kRecs = R == 1 ? 4608 : R == 2 ? 3584 : R == 3 ? 2560 : 2048;
+  static constexpr int kSlots = kRecs / 2 * 3;
+  static constexpr int kLane = kRecs / kThreads;  // records per lane
+  static constexpr int kRows = kRecs / 2;
+  // row list (first record, count): beside the records for one-word records,
+  // whose space the tallies fill, else behind the tallies
+  static constexpr int kList = R == 1 ? kRows : 1;
+  static_assert(kRecs * 8 * R >= kRows * (R == 1 ? 16 : 20), "tallies over the records");
+  static_assert(kRecs * 8 * R + kSlots * 4 + kList * 4 <= 79 * 1024, "small owner LDS");
+  static_assert(kRecs % kThreads == 0 && kSlots % 4 == 0 && kRows % 4 == 0, "even shares");
+  static_assert(kLane * (kThreads / 64) <= 128, "two counts per lane in the row scan");
+};
+
+int own_small_records(uint32_t k) {
+  switch (own_record_words(k)) {
+    case 1: return SmallShape<1>::kRecs;
+    case 2: return SmallShape<2>::kRecs;
+    case 3: return SmallShape<3>::kRecs;
+    default: return SmallShape<4>::kRecs;
+  }
+}
+
+// Do two records hold the same key (all bits but the extension byte)?
+template <int R>
+__device__ __forceinline__ bool same_key(const uint64_t (&a)[R], const uint64_t* b) {
+  uint64_t d = (a[R - 1] ^ b[R - 1]) >> 6;
+#pragma unroll
+  for (int w = 0; w + 1 < R; ++w) d |= a[w] ^ b[w];
+  return d == 0;
+}
+
+template <int R>
+__global__ __launch_bounds__(SmallShape<R>::kThreads, 4) void k_own_count(OwnCountArgs a) {
+  using Shape = SmallShape<R>;
+  constexpr int NT = Shape::kThreads, NB = Shape::kLane, S = Shape::kSlots, NW = NT / 64;
+  constexpr int NE = (NB + 3) / 4;  // words of extension bytes
+  constexpr int kGroup = 3;  // records of a lane whose hashes and claims are issued together
+  __shared__ __align__(16) uint64_t s_rec[Shape::kRecs * R];  // records, then tallies
+  __shared__ __align__(16) uint32_t s_slot[S];
+  __shared__ uint32_t s_c[128];    // rows of each (record column, wave)
+  __shared__ uint32_t s_keys[2];   // keys of this owner, of the next
+  __shared__ uint64_t s_chunk;
+  __shared__ uint64_t s_red[NW];
+  __shared__ uint64_t s_clock;
+  // over the records: the rows' tallies (left A C, G T, right A C, G T)
+  uint4* s_tal = reinterpret_cast<uint4*>(s_rec);
+  uint32_t* s_tal32 = reinterpret_cast<uint32_t*>(s_rec);
+  __shared__ uint32_t s_list1[Shape::kList];
+  uint32_t* s_list = R == 1 ? s_list1 : s_tal32 + 4 * Shape::kRows;
+  int tid = threadIdx.x;
+  const int lane = tid & 63, wave = tid >> 6;
+  const uint32_t k = a.k;
+  const int W = (int)(k + 31) / 32;
+  const int rest_bits = own_rest_bits(k), dw = rest_bits >> 6, doff = rest_bits & 63;
+  uint64_t st_cur = 0, st_end = 0;  // the block's staging chunk (uniform)
+  uint32_t n_first = 0, n_pass = 0;              // per lane (windows number under 2^32)
+  uint32_t n_keys = 0, n_rows = 0;               // per wave, per block
+  uint32_t fullest = 0, par = 0;
+  bool spilt = false;  // staging ran out (uniform)
+  if (tid < 128) s_c[tid] = 0;
+  // optional phase clocks of thread 0
+#define PROF_MARK(e)                                                                \
+  if (a.prof && tid_ == 0) {                                                        \
+    const uint64_t now_ = wall_clock64();                                           \
+    if ((e) > 0) atomicAdd(&a.prof[(e) - 1], (unsigned long long)(now_ - s_clock)); \
+    s_clock = now_;                                                                 \
+  }
+  const int tid_ = threadIdx.x;
+  if (tid < 2) s_keys[tid] = 0;
+  for (uint32_t sb = blockIdx.x; sb < a.n_owners; sb += gridDim.x) {
+    // keeps the addresses that depend on tid alone from being held in
+    // registers across owners
+    asm volatile("" : "+v"(tid));
+    const uint64_t r0 = a.start2[sb];
+    const uint64_t n64 = a.start2[sb + 1] - r0;
+    if (n64 > a.n_small) continue;
+    const uint32_t n = (uint32_t)n64;
+    if (n == 0) {
+      if (tid == 0) {
+        a.rows_sb[sb] = 0;
+        a.row_off[sb] = 0;
+      }
+      continue;
+    }
+    const uint64_t digit = a.owner_bucket[sb];
+    const int nq = (int)((n + NT - 1) / NT);  // record columns in use (uniform)
+    PROF_MARK(0);
+    // ---- the records, and free slots
+    uint64_t v[NB][R];
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+      const uint32_t r = q * NT + tid;
+#pragma unroll
+      for (int w = 0; w < R; ++w) v[q][w] = 0;
+      if (q < nq && r < n) load_record<R>(a.rec, r0 + r, v[q]);
+    }
+    for (int i = tid; i < S / 4; i += NT) reinterpret_cast<uint4*>(s_slot)[i] = make_uint4(0, 0, 0, 0);
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+      const uint32_t r = q * NT + tid;
+      if (q < nq && r < n) {
+#pragma unroll
+        for (int w = 0; w < R; ++w) s_rec[r * R + w] = v[q][w];
+      }
+    }
+    lds_barrier();
+    PROF_MARK(1);
+    // ---- every record finds its key's slot or claims a free one; each step
+    // is issued for a group of a lane's records before the next
+    uint32_t at[NB];
+#pragma unroll
+    for (int q = 0; q < NB; ++q) at[q] = 0;
+    uint32_t first = 0;  // bit q: record q is its key's first
+#pragma unroll
+    for (int q0 = 0; q0 < NB; q0 += kGroup) {
+      if (q0 >= nq) continue;
+      uint32_t old[kGroup];
+#pragma unroll
+      for (int g = 0; g < kGroup; ++g) {
+        const int q = q0 + g;
+        if (q >= NB || q >= nq) continue;
+        uint64_t key[R], h = 0;
+        const uint64_t K[4] = {0x9e3779b97f4a7c15ull, 0xc2b2ae3d27d4eb4full, 0x165667b19e3779f9ull,
+                               0xd6e8feb86659fd93ull};
+        record_key<R>(v[q], key);
+#pragma unroll
+        for (int w = 0; w < R; ++w) h += key[w] * K[w];
+        h ^= h >> 29;
+        at[q] = __umulhi((uint32_t)(h >> 32), (uint32_t)S);
+        const uint32_t r = q * NT + tid;
+        old[g] = r < n ? atomicCAS(&s_slot[at[q]], 0u, (r + 1) | 0x10000u) : 0u;
+      }
+#pragma unroll
+      for (int g = 0; g < kGroup; ++g) {
+        const int q = q0 + g;
+        if (q >= NB || q >= nq) continue;
+        const uint32_t r = q * NT + tid;
+        if (r >= n) continue;
+        uint32_t o = old[g], i = at[q];
+        // free slots outnumber the records: every search ends
+        while (o != 0 && !same_key<R>(v[q], s_rec + ((o & 0xffffu) - 1) * R)) {
+          if (++i == (uint32_t)S) i = 0;
+          o = atomicCAS(&s_slot[i], 0u, (r + 1) | 0x10000u);
+        }
+        at[q] = i;
+        if (o == 0)
+          first |= 1u << q;
+        else
+          atomicAdd(&s_slot[i], 0x10000u);
+      }
+      __builtin_amdgcn_sched_barrier(0);  // one group's registers at a time
+    }
+    uint32_t ext[NE];  // the records' extension bytes (their keys are not needed again)
+#pragma unroll
+    for (int e = 0; e < NE; ++e) ext[e] = 0;
+#pragma unroll
+    for (int q = 0; q < NB; ++q) ext[q / 4] |= (uint32_t)(v[q][R - 1] & 63u) << (8 * (q % 4));
+    PROF_MARK(2);
+    lds_barrier();
+    PROF_MARK(3);
+    // ---- rows: keys with min_count occurrences, numbered in the order of
+    // their first records (columns of 64 records, one per wave and q), so
+    // that neighbouring lanes write neighbouring rows
+    uint32_t keep = 0, nkeys = 0;
+    const uint32_t thr = a.use_bloom ? 2u : 1u;  // the screen's: keys seen twice
+    n_first += __popc(first);
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+      if (q >= nq) continue;
+      const uint32_t c = (first >> q) & 1u ? s_slot[at[q]] >> 16 : 0u;
+      const bool row = c >= max(a.min_count, 1u);
+      keep |= row ? 1u << q : 0u;
+      const uint64_t m = __ballot(row);
+      if (lane == 0) s_c[q * NW + wave] = (uint32_t)__popcll(m);
+      n_pass += c >= thr ? c : 0u;
+      nkeys += (uint32_t)__popcll(__ballot(c >= thr));
+    }
+    n_keys += nkeys;
+    if (lane == 0) atomicAdd(&s_keys[par], nkeys);
+    lds_barrier();
+    PROF_MARK(4);
+    const bool used = 2 * lane < nq * NW;  // NW is even
+    const uint32_t x0 = used ? s_c[2 * lane] : 0u, x1 = used ? s_c[2 * lane + 1] : 0u;
+    uint32_t incl = x0 + x1;
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t y = __shfl_up(incl, o);
+      if (lane >= o) incl += y;
+    }
+    const uint32_t rows = __shfl(incl, 63);  // uniform over the block
+    // first row of column (q, wave): NW is even, so a wave's columns are all
+    // even or all odd
+    const uint32_t mine = incl - x0 - x1 + ((wave & 1) ? x0 : 0u);
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+      if (q >= nq) continue;
+      const uint32_t base = __shfl(mine, (q * NW + wave) >> 1);
+      const uint64_t m = __ballot((keep >> q) & 1u);
+      if (!((first >> q) & 1u)) continue;
+      const uint32_t w = s_slot[at[q]];
+      const uint32_t j = base + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                          __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+      const bool row = (keep >> q) & 1u;
+      // the word now holds the key's row + 1 (0: no row), its count stays
+      s_slot[at[q]] = (w & 0xffff0000u) | (row ? j + 1 : 0u);
+      if (row && j < (uint32_t)Shape::kRows) {
+        s_list[j] = (w & 0xffff0000u) | (uint32_t)(q * NT + tid);
+        s_tal[j] = make_uint4(0, 0, 0, 0);
+      }
+    }
+    if (tid == 0) {
+      fullest = max(fullest, s_keys[par]);
+      s_keys[par ^ 1] = 0;
+    }
+    par ^= 1;
+    // staging rows, a chunk from the shared cursor at a time
+    uint64_t base_row;
+    bool fits = true;
+    const bool fresh = !a.st_fixed && st_cur + rows > st_end;  // uniform
+    const uint64_t want = rows > a.st_chunk ? rows : a.st_chunk;
+    if (fresh && tid == 0) s_chunk = atomicAdd(a.st_cursor, (unsigned long long)want);
+    lds_barrier();
+    PROF_MARK(5);
+    uint64_t u[R];
+#pragma unroll
+    for (int w = 0; w < R; ++w) u[w] = 0;
+    if ((uint32_t)tid < rows) load_record<R>(a.rec, r0 + (s_list[tid] & 0xffffu), u);
+    if (a.st_fixed) {
+      base_row = a.st_fixed[sb];
+    } else {
+      if (fresh) {
+        st_cur = s_chunk;
+        st_end = st_cur + want;
+      }
+      base_row = st_cur;
+      fits = base_row + rows <= a.st_cap;
+      st_cur += rows;
+    }
+    spilt |= !fits;
+    n_rows += rows;
+    // ---- tallies, then the rows
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+      if (q >= nq || (uint32_t)(q * NT + tid) >= n) continue;
+      const uint32_t j = (s_slot[at[q]] & 0xffffu) - 1;
+      if (j >= (uint32_t)Shape::kRows) continue;  // no row (wrapped)
+      const uint32_t e6 = ext[q / 4] >> (8 * (q % 4));
+      if (e6 & 32u) atomicAdd(&s_tal32[4 * j + ((e6 >> 4) & 1u)], (e6 & 8u) ? 0x10000u : 1u);
+      if (e6 & 4u) atomicAdd(&s_tal32[4 * j + 2 + ((e6 >> 1) & 1u)], (e6 & 1u) ? 0x10000u : 1u);
+    }
+    lds_barrier();
+    PROF_MARK(6);
+    for (uint32_t j = tid; j < (fits ? rows : 0u); j += NT) {
+      const uint32_t cnt = s_list[j] >> 16;
+      uint64_t f[R];
+      if (j >= (uint32_t)NT) load_record<R>(a.rec, r0 + (s_list[j] & 0xffffu), u);
+      record_key<R>(u, f);
+      const uint4 t = s_tal[j];
+      const uint64_t row = base_row + j;
+#pragma unroll
+      for (int w = 0; w <= R; ++w) {  // the whole key, least significant word first
+        uint64_t x = w < R ? f[R - 1 - w] : 0ull;
+        if (w == dw) x |= digit << doff;
+        if (w == dw + 1 && doff > 0) x |= digit >> (64 - doff);
+        if (w < W) a.st_keys[row * W + (W - 1 - w)] = x;
+      }
+      const uint32_t l[4] = {t.x & 0xffffu, t.x >> 16, t.y & 0xffffu, t.y >> 16};
+      const uint32_t rr[4] = {t.z & 0xffffu, t.z >> 16, t.w & 0xffffu, t.w >> 16};
+      a.st_counts[row] = cnt;
+      uint4* ep = reinterpret_cast<uint4*>(a.st_ext + row * 8);
+      ep[0] = make_uint4(l[0], l[1], l[2], l[3]);
+      ep[1] = make_uint4(rr[0], rr[1], rr[2], rr[3]);
+      reinterpret_cast<uint16_t*>(a.st_codes)[row] =
+          (uint16_t)((uint32_t)side_code(l, cnt, a.t_min_ext, a.t_base, a.err_ppm) |
+                     ((uint32_t)side_code(rr, cnt, a.t_min_ext, a.t_base, a.err_ppm) << 8));
+    }
+    PROF_MARK(7);
+    if (tid == 0) {
+      a.rows_sb[sb] = rows;
+      a.row_off[sb] = rows;
+      a.st_off[sb] = base_row;
+    }
+    lds_barrier();  // the rows have left LDS: the next owner may use it
+    PROF_MARK(8);
+  }
+#undef PROF_MARK
+  // ---- statistics of the block's owners: first and second sightings (as an
+  // exact Bloom screen would see them), records counted, keys, rows
+  unsigned long long* sc = a.ctr + (uint64_t)(blockIdx.x % kOwnStripes) * kCtrCount;
+  __syncthreads();
+  if (a.use_bloom) block_add(&sc[kCtrL1New], n_first, s_red);
+  __syncthreads();
+  block_add(&sc[kCtrPassed], n_pass, s_red);
+  if (lane == 0 && n_keys) {
+    atomicAdd(&sc[kCtrClaimed], (unsigned long long)n_keys);
+    if (a.use_bloom) atomicAdd(&sc[kCtrL2New], (unsigned long long)n_keys);
+  }
+  if (tid == 0) {
+    if (n_rows) atomicAdd(&sc[kCtrRows], (unsigned long long)n_rows);
+    atomicMax(&sc[kCtrWindows], (unsigned long long)fullest);
+    if (spilt) atomicOr(&sc[kCtrStatus], (unsigned long long)kStatusStaging);
+  }
+}
+
 // Owners' rows from staging to the table at the scanned row offsets, in key
 // order (one block per owner; the owner pass leaves them in slot order).
 // The owner's keys share its prefix, so each row's sort key is the next
@@ -1195,29 +1528,45 @@ void launch_own_colscan(const OwnPartArgs& a, uint32_t n_owners, hipStream_t s) 
                      n_owners);
 }
 
-void launch_own_count(const OwnCountArgs& a, uint32_t blocks, hipStream_t s) {
+void launch_own_count(const OwnCountArgs& a, uint32_t cus, bool any_big, hipStream_t s) {
   if (a.n_owners == 0) return;
   const int R = own_record_words(a.k);
   const int C = own_chunks(a.k);  // R - 1 .. R chunks (rest bits + 6 over 64, rest over 62)
-  const dim3 g(blocks < a.n_owners ? blocks : a.n_owners), t(kOwnThreads);
-  if (R == 1) hipLaunchKernelGGL((k_own_count<1, 1>), g, t, 0, s, a);
-  else if (R == 2 && C == 1) hipLaunchKernelGGL((k_own_count<2, 1>), g, t, 0, s, a);
-  else if (R == 2) hipLaunchKernelGGL((k_own_count<2, 2>), g, t, 0, s, a);
-  else if (R == 3 && C == 2) hipLaunchKernelGGL((k_own_count<3, 2>), g, t, 0, s, a);
-  else if (R == 3) hipLaunchKernelGGL((k_own_count<3, 3>), g, t, 0, s, a);
-  else hipLaunchKernelGGL((k_own_count<4, 4>), g, t, 0, s, a);
+  {
+    const dim3 g(2 * cus < a.n_owners ? 2 * cus : a.n_owners), t(SmallShape<1>::kThreads);
+    switch (R) {
+      case 1: hipLaunchKernelGGL(k_own_count<1>, g, t, 0, s, a); break;
+      case 2: hipLaunchKernelGGL(k_own_count<2>, g, t, 0, s, a); break;
+      case 3: hipLaunchKernelGGL(k_own_count<3>, g, t, 0, s, a); break;
+      default: hipLaunchKernelGGL(k_own_count<4>, g, t, 0, s, a); break;
+    }
+  }
+  if (!any_big) return;
+  const dim3 g(cus < a.n_owners ? cus : a.n_owners), t(kOwnThreads);
+  if (R == 1) hipLaunchKernelGGL((k_own_count_big<1, 1>), g, t, 0, s, a);
+  else if (R == 2 && C == 1) hipLaunchKernelGGL((k_own_count_big<2, 1>), g, t, 0, s, a);
+  else if (R == 2) hipLaunchKernelGGL((k_own_count_big<2, 2>), g, t, 0, s, a);
+  else if (R == 3 && C == 2) hipLaunchKernelGGL((k_own_count_big<3, 2>), g, t, 0, s, a);
+  else if (R == 3) hipLaunchKernelGGL((k_own_count_big<3, 3>), g, t, 0, s, a);
+  else hipLaunchKernelGGL((k_own_count_big<4, 4>), g, t, 0, s, a);
 }
+
+constexpr int cmax(int a, int b) { return a > b ? a : b; }
 
 void launch_own_copy(const OwnCopyArgs& a, uint32_t n_owners, hipStream_t s) {
   if (n_owners == 0) return;
-  // rows of an owner at most: the slots of the fewest key chunks a W-word
-  // key can have (W = 1, 2: one chunk; 3: two; 4: three)
+  // rows of an owner at most: a small one's or the slots of a big one, for
+  // the fewest record words (W = 1, 2: one; 3: two; 4: three) and key chunks
+  // (one, two, three) a W-word key can have
   const dim3 g(n_owners), t(kOwnCopyThreads);
+  constexpr int n1 = cmax(SmallShape<1>::kRows, OwnerShape<1>::kSlots);
+  constexpr int n2 = cmax(SmallShape<2>::kRows, OwnerShape<2>::kSlots);
+  constexpr int n3 = cmax(SmallShape<3>::kRows, OwnerShape<3>::kSlots);
   switch (a.W) {
-    case 1: hipLaunchKernelGGL((k_own_copy<1, OwnerShape<1>::kSlots>), g, t, 0, s, a); break;
-    case 2: hipLaunchKernelGGL((k_own_copy<2, OwnerShape<1>::kSlots>), g, t, 0, s, a); break;
-    case 3: hipLaunchKernelGGL((k_own_copy<3, OwnerShape<2>::kSlots>), g, t, 0, s, a); break;
-    default: hipLaunchKernelGGL((k_own_copy<4, OwnerShape<3>::kSlots>), g, t, 0, s, a); break;
+    case 1: hipLaunchKernelGGL((k_own_copy<1, n1>), g, t, 0, s, a); break;
+    case 2: hipLaunchKernelGGL((k_own_copy<2, n1>), g, t, 0, s, a); break;
+    case 3: hipLaunchKernelGGL((k_own_copy<3, n2>), g, t, 0, s, a); break;
+    default: hipLaunchKernelGGL((k_own_copy<4, n3>), g, t, 0, s, a); break;
   }
 }
 
