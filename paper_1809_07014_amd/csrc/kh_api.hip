@@ -633,6 +633,7 @@ static int count_owned(kh_ctx* ctx, Packed& pk, const kh_params& p, hipStream_t 
     pa.big = big.p;
     pa.n_big = big.p + 2 * (n_owners / 2 + 1);
     pa.n_small = n_small;
+    pa.n_chunks = (uint32_t)n_chunks;
     pa.k = k;
     pa.p1 = (uint32_t)p1;
     launch_fill_u64(reinterpret_cast<uint64_t*>(pa.n_big), 1, 0ull, s);

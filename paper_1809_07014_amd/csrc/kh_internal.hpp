@@ -226,6 +226,7 @@ struct OwnPartArgs {
   uint32_t* big;           // owners of more than n_small records (k_own_colscan)
   uint32_t* n_big;         // their number (zero before)
   uint32_t n_small;
+  uint32_t n_chunks;
   uint32_t k, p1;
 };
 

@@ -331,8 +331,9 @@ __global__ __launch_bounds__(kOwnRouteThreads) void k_own_hist(OwnRouteArgs a) {
   block_add(&a.ctr[kCtrWindows], nwin, s_red);
 }
 
-// Level-1 emit: the same routing tiles as k_own_hist, taken in batches (two
-// tiles for one-word records, else one).  A lane forms four consecutive
+// Level-1 emit: the same routing tiles as k_own_hist, taken in batches (three
+// tiles for one-word records, two for two words, else one: what the LDS
+// holds).  A lane forms four consecutive
 // windows of a tile, the first one's words read from the staged bases, each
 // next one's by shifting one base in, and keeps their records; the bucket
 // counts' atomics return each record's rank in its bucket, so after a scan of
@@ -342,12 +343,12 @@ __global__ __launch_bounds__(kOwnRouteThreads) void k_own_hist(OwnRouteArgs a) {
 //
 // One-word records are bound by the LDS exchange and its barriers at one block
 // per CU, longer ones more and more by their stores.  10M reads of 150 bases:
-// k = 21, 33, 55, 77, 99 take 7.6, 7.5, 10.2, 12.0 and 10.9 ms, from 14.1,
+// k = 21, 33, 55, 77, 99 take 7.3, 7.5, 9.3, 12.4 and 10.9 ms, from 14.1,
 // 15.7, 17.4, 19.0 and 19.4 ms when each window looked up its own validity and
 // extension bits and a record's bucket place was found by a second atomic.
 template <int R>
 struct EmitBatch {
-  static constexpr int kTiles = R == 1 ? 2 : 1;       // routing tiles
+  static constexpr int kTiles = R == 1 ? 3 : R == 2 ? 2 : 1;  // routing tiles
   static constexpr int kCap = kTiles * kOwnTile;      // records per batch
 };
 
@@ -479,16 +480,23 @@ __global__ __launch_bounds__(kOwnRouteThreads) void k_own_emit_staged(OwnRouteAr
 
 // ------------------------------------------------------ level 2 route ----
 
-// Records per level-2 chunk (one block): 8,192 record words.
+// Records per level-2 chunk (one block): 12,288 record words, as many as one
+// block's share of the LDS holds beside the digits' tables.  Longer chunks mean
+// longer runs: 10M reads, k = 21 (450 owners per bucket) 8.4 ms with 12,288
+// words, 9.8 with 8,192, before neighbouring chunks shared an XCD.
 template <int R>
 struct PartShape {
-  static constexpr int kChunk = R == 1 ? 8192 : (R == 2 ? 4096 : (R <= 4 ? 2048 : 1024));
+  static constexpr int kChunk = 12288 / R / kOwnPartThreads * kOwnPartThreads;
   static constexpr int kPerThread = kChunk / kOwnPartThreads;
 };
 
 int own_chunk_records(uint32_t k) {
-  const int R = own_record_words(k);
-  return R == 1 ? 8192 : (R == 2 ? 4096 : (R <= 4 ? 2048 : 1024));
+  switch (own_record_words(k)) {
+    case 1: return PartShape<1>::kChunk;
+    case 2: return PartShape<2>::kChunk;
+    case 3: return PartShape<3>::kChunk;
+    default: return PartShape<4>::kChunk;
+  }
 }
 
 // The bucket of every owner and of every level-2 chunk (one block per
@@ -540,64 +548,79 @@ __global__ __launch_bounds__(kOwnPartThreads) void k_own_scatter2(OwnPartArgs a)
   constexpr int PT = PartShape<R>::kPerThread;
   __shared__ uint64_t s_rec[CH * R];
   __shared__ uint16_t s_bin[CH];
-  __shared__ uint32_t s_cnt[1 << kOwnL2Max];
-  __shared__ uint32_t s_start[1 << kOwnL2Max];
-  __shared__ uint32_t s_cur[1 << kOwnL2Max];
+  __shared__ uint32_t s_cnt[1 << kOwnL2Max];  // counts, then places in the chunk
+  __shared__ uint32_t s_dst[1 << kOwnL2Max];  // cursor minus place
   __shared__ uint32_t s_w[kOwnPartThreads / 64];
   const int tid = threadIdx.x;
-  const int b = a.chunk_bucket[blockIdx.x];
+  // consecutive chunks to one XCD (blocks go round robin over 8): the runs of
+  // neighbouring chunks adjoin, and the line they share is completed in one L2
+  // instead of leaving two in parts.  k = 21, 55, 77, 99 of 10M reads: 4.6,
+  // 6.4, 7.6 and 6.7 ms (4.5 TB/s), from 8.4, 11.5, 15.8 and 11.4 ms.
+  const uint32_t id = (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  if (id >= a.n_chunks) return;
+  const int b = a.chunk_bucket[id];
   const OwnBucket bk = a.buckets[b];
-  const uint32_t c = blockIdx.x - bk.cbase;
+  const uint32_t c = id - bk.cbase;
   const int nbins = 1 << bk.p2;
-  for (int i = tid; i < nbins; i += kOwnPartThreads) {
-    s_cnt[i] = 0;
-    s_cur[i] = a.start2[bk.sbbase + i] + a.m[bk.mbase + (uint64_t)c * nbins + i];
-  }
-  lds_barrier();
   const uint64_t r0 = bk.start + (uint64_t)c * CH;
   const uint64_t r1 = r0 + (uint64_t)CH < bk.start + bk.n ? r0 + (uint64_t)CH : bk.start + bk.n;
-  const int roff = 64 * R - 2 * (int)a.k - 6 + (int)a.p1;
+  const uint32_t n = (uint32_t)(r1 - r0);
   uint64_t v[PT][R];
-  uint32_t bin[PT], rank[PT];
 #pragma unroll
   for (int q = 0; q < PT; ++q) {
-    const uint64_t r = r0 + (uint64_t)q * kOwnPartThreads + tid;
-    bin[q] = 0xffffffffu;
-    rank[q] = 0;
+    const uint32_t r = (uint32_t)q * kOwnPartThreads + tid;
 #pragma unroll
     for (int w = 0; w < R; ++w) v[q][w] = 0;
-    if (r < r1) load_record<R>(a.rec_in, r, v[q]);
+    if (r < n) load_record<R>(a.rec_in, r0 + r, v[q]);
   }
+  // the two digits of this thread (nbins <= 2 x kOwnPartThreads) and their
+  // cursors
+  uint32_t cur[2] = {0, 0};
 #pragma unroll
-  for (int q = 0; q < PT; ++q) {
-    const uint64_t r = r0 + (uint64_t)q * kOwnPartThreads + tid;
-    if (r < r1) {
-      bin[q] = top_bits<R>(v[q], roff, (int)bk.p2);
-      rank[q] = atomicAdd(&s_cnt[bin[q]], 1u);
+  for (int e = 0; e < 2; ++e) {
+    const int d = 2 * tid + e;
+    if (d < nbins) {
+      cur[e] = a.start2[bk.sbbase + d] + a.m[bk.mbase + (uint64_t)c * nbins + d];
+      s_cnt[d] = 0;
     }
   }
   lds_barrier();
-  // bucket starts: nbins <= 2 * kOwnPartThreads values, two per thread
+  const int roff = 64 * R - 2 * (int)a.k - 6 + (int)a.p1;
+  uint32_t br[PT];  // digit << 16 | rank among the chunk's records of that digit
+#pragma unroll
+  for (int q = 0; q < PT; ++q) {
+    br[q] = ~0u;
+    if ((uint32_t)q * kOwnPartThreads + tid < n) {
+      const uint32_t d = top_bits<R>(v[q], roff, (int)bk.p2);
+      br[q] = (d << 16) | atomicAdd(&s_cnt[d], 1u);
+    }
+  }
+  lds_barrier();
   const uint32_t c0 = 2 * tid < nbins ? s_cnt[2 * tid] : 0u;
   const uint32_t c1 = 2 * tid + 1 < nbins ? s_cnt[2 * tid + 1] : 0u;
   uint32_t excl = 0;
   block_excl_scan(c0 + c1, excl, s_w);
-  if (2 * tid < nbins) s_start[2 * tid] = excl;
-  if (2 * tid + 1 < nbins) s_start[2 * tid + 1] = excl + c0;
+  if (2 * tid < nbins) {
+    s_cnt[2 * tid] = excl;
+    s_dst[2 * tid] = cur[0] - excl;
+  }
+  if (2 * tid + 1 < nbins) {
+    s_cnt[2 * tid + 1] = excl + c0;
+    s_dst[2 * tid + 1] = cur[1] - excl - c0;
+  }
   lds_barrier();
 #pragma unroll
   for (int q = 0; q < PT; ++q) {
-    if (bin[q] == 0xffffffffu) continue;
-    const uint32_t pos = s_start[bin[q]] + rank[q];
+    if (br[q] == ~0u) continue;
+    const uint32_t d = br[q] >> 16, pos = s_cnt[d] + (br[q] & 0xffffu);
 #pragma unroll
     for (int w = 0; w < R; ++w) s_rec[pos * R + w] = v[q][w];
-    s_bin[pos] = (uint16_t)bin[q];
+    s_bin[pos] = (uint16_t)d;
   }
   lds_barrier();
-  const uint32_t n = (uint32_t)(r1 - r0);
   for (uint32_t i = tid; i < n * R; i += kOwnPartThreads) {
-    const uint32_t rr = i / R, d = s_bin[rr];
-    a.rec_out[((uint64_t)s_cur[d] + (rr - s_start[d])) * R + (i - rr * R)] = s_rec[i];
+    const uint32_t rr = i / R;
+    a.rec_out[(uint64_t)(s_dst[s_bin[rr]] + rr) * R + (i - rr * R)] = s_rec[i];
   }
 }
 
@@ -1509,11 +1532,12 @@ void launch_own_part(const OwnPartArgs& a, uint32_t n_chunks, int scatter, hipSt
       default: hipLaunchKernelGGL(k_own_hist2<4>, g, t, 0, s, a); break;
     }
   } else {
+    const dim3 g8((n_chunks + 7) / 8 * 8);
     switch (R) {
-      case 1: hipLaunchKernelGGL(k_own_scatter2<1>, g, t, 0, s, a); break;
-      case 2: hipLaunchKernelGGL(k_own_scatter2<2>, g, t, 0, s, a); break;
-      case 3: hipLaunchKernelGGL(k_own_scatter2<3>, g, t, 0, s, a); break;
-      default: hipLaunchKernelGGL(k_own_scatter2<4>, g, t, 0, s, a); break;
+      case 1: hipLaunchKernelGGL(k_own_scatter2<1>, g8, t, 0, s, a); break;
+      case 2: hipLaunchKernelGGL(k_own_scatter2<2>, g8, t, 0, s, a); break;
+      case 3: hipLaunchKernelGGL(k_own_scatter2<3>, g8, t, 0, s, a); break;
+      default: hipLaunchKernelGGL(k_own_scatter2<4>, g8, t, 0, s, a); break;
     }
   }
 }
