@@ -173,11 +173,7 @@ static int pack_reads(kh_ctx* ctx, const kh_reads* r, const kh_params& p,
   int64_t n = 0;
   if (r->n_reads > 0) {
     if (r->on_device) {
-      int64_t ends[1];
-      HIP_TRY(hipMemcpyAsync(ends, r->offsets + r->n_reads, sizeof(int64_t),
-                             hipMemcpyDeviceToHost, s));
-      HIP_TRY(hipStreamSynchronize(s));
-      n = ends[0];
+      KH_TRY(fetch(ctx, s, {&n, r->offsets + r->n_reads, sizeof n}));
     } else {
       if (r->offsets[0] != 0) return fail(KH_EINVAL, "offsets[0] must be 0");
       for (int64_t i = 0; i < r->n_reads; ++i)
@@ -247,10 +243,6 @@ static int pack_reads(kh_ctx* ctx, const kh_reads* r, const kh_params& p,
   KH_TRY(pk.hq.alloc((uint64_t)pk.plane_words));
   KH_TRY(pk.bad.alloc((uint64_t)pk.plane_words));
   KH_TRY(pk.st.alloc((uint64_t)pk.plane_words));
-  // pad words beyond n: no base, not a start
-  launch_fill_u64(pk.bases.p, (uint64_t)pk.base_words, 0ull, s);
-  launch_fill_u64(pk.hq.p, (uint64_t)pk.plane_words, 0ull, s);
-  launch_fill_u64(pk.bad.p, (uint64_t)pk.plane_words, ~0ull, s);
   PackArgs a{};
   a.seq = seq;
   a.qual = qual;
@@ -264,14 +256,43 @@ static int pack_reads(kh_ctx* ctx, const kh_reads* r, const kh_params& p,
   a.bad = pk.bad.p;
   a.st = pk.st.p;
   a.plane_words = pk.plane_words;
+  a.base_words = pk.base_words;
+  a.inited = 1;
   a.ctr = ctx->ctr;
-  launch_fill_u64(reinterpret_cast<uint64_t*>(ctx->ctr), kCtrCount, 0ull, s);
+  launch_plane_init(a, s);
   pk.pa = a;
   if (streamed)
     launch_mark_starts(a, s);
   else
     launch_pack(a, s);
   HIP_TRY(hipGetLastError());
+  return KH_OK;
+}
+
+int kh::fetch(kh_ctx* ctx, hipStream_t s, Fetch a, Fetch b, Fetch c) {
+  const Fetch f[3] = {a, b, c};
+  uint64_t words = 0;
+  for (const Fetch& x : f) words += x.bytes / 4;
+  if (ctx->box && words <= kBoxWords) {
+    PostArgs p{};
+    for (int i = 0; i < 3; ++i) {
+      p.src[i] = static_cast<const uint32_t*>(f[i].src);
+      p.words[i] = (uint32_t)(f[i].bytes / 4);
+    }
+    p.dst = ctx->box;
+    launch_post(p, s);
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(hipStreamSynchronize(s));
+    const uint32_t* at = ctx->box;
+    for (const Fetch& x : f) {
+      if (x.bytes) std::memcpy(x.dst, at, x.bytes);
+      at += x.bytes / 4;
+    }
+    return KH_OK;
+  }
+  for (const Fetch& x : f)
+    if (x.bytes) HIP_TRY(hipMemcpyAsync(x.dst, x.src, x.bytes, hipMemcpyDeviceToHost, s));
+  HIP_TRY(hipStreamSynchronize(s));
   return KH_OK;
 }
 
@@ -284,7 +305,7 @@ int kh::read_ctr_at(const unsigned long long* ctr, hipStream_t s,
 }
 
 int kh::read_ctr(kh_ctx* ctx, hipStream_t s, uint64_t (&c)[kCtrCount]) {
-  return read_ctr_at(ctx->ctr, s, c);
+  return fetch(ctx, s, {c, ctx->ctr, sizeof(uint64_t) * kCtrCount});
 }
 
 int kh::make_table(kh_ctx* ctx, uint32_t k, kh_table** out) {
@@ -334,7 +355,7 @@ int kh::finish_rows(kh_ctx* ctx, unsigned long long* ctr, uint8_t* table,
   launch_classify(ca, s);
   HIP_TRY(hipGetLastError());
   mark(ctx, 7, s);
-  KH_TRY(read_ctr_at(ctr, s, c));
+  KH_TRY(fetch(ctx, s, {c, ctr, sizeof c}));
   const int64_t rows = (int64_t)c[kCtrRows];
   if (t->dst_cap >= 0 && rows > t->dst_cap) {
     t->n_rows = rows;
@@ -398,7 +419,7 @@ int kh::finish_rows(kh_ctx* ctx, unsigned long long* ctr, uint8_t* table,
     if (2 * k > 64) {
       launch_fix_ties(pfx_sorted, idx_sorted, rows, table, k, ctr, s);
       HIP_TRY(hipGetLastError());
-      KH_TRY(read_ctr_at(ctr, s, c));
+      KH_TRY(fetch(ctx, s, {c, ctr, sizeof c}));
       if (c[kCtrStatus] & kStatusLongTies) {
         // many keys share their top 20 bases: sort by the full key instead
         Buf<uint64_t> ka(pool), kb(pool);
@@ -502,9 +523,10 @@ static int count_owned(kh_ctx* ctx, Packed& pk, const kh_params& p, hipStream_t 
 
   // ---- level 1: bucket histogram matrix, its scan, the bucket starts
   Buf<uint32_t> h1(pool), b1(pool), part(pool);
-  KH_TRY(h1.alloc((uint64_t)nb1 * grid));
-  KH_TRY(b1.alloc((uint64_t)nb1));
-  KH_TRY(part.alloc(scan_tmp_words((int64_t)nb1 * grid)));
+  // (one more entry: the total)
+  KH_TRY(h1.alloc((uint64_t)nb1 * grid + 1));
+  KH_TRY(b1.alloc((uint64_t)nb1 + 1));
+  KH_TRY(part.alloc(scan_tmp_words((int64_t)nb1 * grid + 1)));
   Buf<uint64_t> win(pool), lx(pool), rx(pool);
   KH_TRY(win.alloc((uint64_t)pk.plane_words));
   KH_TRY(lx.alloc((uint64_t)pk.plane_words));
@@ -529,13 +551,12 @@ static int count_owned(kh_ctx* ctx, Packed& pk, const kh_params& p, hipStream_t 
   mark(ctx, 2, s);
   launch_own_planes(ra, s);
   launch_own_hist(ra, grid, s);
-  exclusive_scan_u32(h1.p, (int64_t)nb1 * grid, part.p, s);
-  launch_gather_strided(h1.p, (uint64_t)grid, (uint32_t)nb1, b1.p, s);
+  exclusive_scan_u32(h1.p, (int64_t)nb1 * grid + 1, part.p, s);
+  launch_gather_strided(h1.p, (uint64_t)grid, (uint32_t)nb1 + 1, b1.p, s);
   HIP_TRY(hipGetLastError());
   std::vector<uint32_t> hb(nb1);
-  HIP_TRY(hipMemcpyAsync(hb.data(), b1.p, sizeof(uint32_t) * nb1, hipMemcpyDeviceToHost, s));
   uint64_t c[kCtrCount];
-  KH_TRY(read_ctr_at(ctr, s, c));
+  KH_TRY(fetch(ctx, s, {c, ctr, sizeof c}, {hb.data(), b1.p, sizeof(uint32_t) * nb1}));
   if (c[kCtrStatus] & kStatusBadOffsets)
     return fail(KH_EINVAL, "offsets are not non-decreasing from 0 to the base count");
   const uint64_t n_rec = c[kCtrWindows];
@@ -603,55 +624,66 @@ static int count_owned(kh_ctx* ctx, Packed& pk, const kh_params& p, hipStream_t 
       n_chunks += x.chunks;
       m_size += (uint64_t)x.chunks << p2;
     }
+    // No bucket is split and all are small owners (few reads): the buckets are
+    // the owners, level 2 would only copy their records.  6,667 reads of 150
+    // bases, k = 21: the call 333 -> 190 us, with the host reading results
+    // from pinned words and the planes initialised in one launch.
+    const uint64_t fullest = *std::max_element(nbk.begin(), nbk.end());
+    const bool flat = n_owners == (uint64_t)nb1 && fullest <= n_small;
     Buf<OwnBucket> dbk(pool);
     Buf<uint32_t> m(pool), start2(pool), rows_sb(pool), row_off(pool), part2(pool), big(pool);
     Buf<unsigned long long> stripes(pool);
     Buf<uint16_t> owner_bucket(pool), chunk_bucket(pool);
     Buf<uint8_t> owner_pfx(pool);
-    KH_TRY(owner_bucket.alloc(n_owners));
-    KH_TRY(owner_pfx.alloc(n_owners));
-    KH_TRY(chunk_bucket.alloc(std::max<uint64_t>(n_chunks, 1)));
-    KH_TRY(dbk.alloc(nb1));
-    KH_TRY(m.alloc(std::max<uint64_t>(m_size, 1)));
-    KH_TRY(start2.alloc(n_owners + 1));
-    KH_TRY(big.alloc(2 * (n_owners / 2 + 1) + 2));  // the list, then its length
     KH_TRY(rows_sb.alloc(n_owners));
     KH_TRY(row_off.alloc(n_owners));
     KH_TRY(part2.alloc(scan_tmp_words((int64_t)n_owners + 1)));
     KH_TRY(stripes.alloc((uint64_t)kOwnStripes * kCtrCount + 1));  // + staging cursor
-    HIP_TRY(hipMemcpyAsync(dbk.p, bk.data(), sizeof(OwnBucket) * nb1, hipMemcpyHostToDevice, s));
     OwnPartArgs pa{};
-    pa.rec_in = rec1.p;
-    pa.rec_out = rec2.p;
-    pa.buckets = dbk.p;
-    pa.n_buckets = nb1;
-    pa.m = m.p;
-    pa.start2 = start2.p;
-    pa.owner_bucket = owner_bucket.p;
-    pa.owner_pfx = owner_pfx.p;
-    pa.chunk_bucket = chunk_bucket.p;
-    pa.big = big.p;
-    pa.n_big = big.p + 2 * (n_owners / 2 + 1);
-    pa.n_small = n_small;
-    pa.n_chunks = (uint32_t)n_chunks;
-    pa.k = k;
-    pa.p1 = (uint32_t)p1;
-    launch_fill_u64(reinterpret_cast<uint64_t*>(pa.n_big), 1, 0ull, s);
-    launch_own_maps(pa, s);
-    launch_own_part(pa, (uint32_t)n_chunks, 0, s);
-    launch_own_colscan(pa, (uint32_t)n_owners, s);
-    exclusive_scan_u32(start2.p, (int64_t)n_owners + 1, part2.p, s);
-    launch_own_part(pa, (uint32_t)n_chunks, 1, s);
-    HIP_TRY(hipGetLastError());
+    if (!flat) {
+      KH_TRY(owner_bucket.alloc(n_owners));
+      KH_TRY(owner_pfx.alloc(n_owners));
+      KH_TRY(chunk_bucket.alloc(std::max<uint64_t>(n_chunks, 1)));
+      KH_TRY(dbk.alloc(nb1));
+      KH_TRY(m.alloc(std::max<uint64_t>(m_size, 1)));
+      KH_TRY(start2.alloc(n_owners + 1));
+      KH_TRY(big.alloc(2 * (n_owners / 2 + 1) + 2));  // the list, then its length
+      const void* from = bk.data();
+      static_assert(sizeof(OwnBucket) * kOwnL1Max <= kBoxWords * 4, "buckets fit the pinned words");
+      if (ctx->box) from = std::memcpy(ctx->box, bk.data(), sizeof(OwnBucket) * nb1);
+      HIP_TRY(hipMemcpyAsync(dbk.p, from, sizeof(OwnBucket) * nb1, hipMemcpyHostToDevice, s));
+      pa.rec_in = rec1.p;
+      pa.rec_out = rec2.p;
+      pa.buckets = dbk.p;
+      pa.n_buckets = nb1;
+      pa.m = m.p;
+      pa.start2 = start2.p;
+      pa.owner_bucket = owner_bucket.p;
+      pa.owner_pfx = owner_pfx.p;
+      pa.chunk_bucket = chunk_bucket.p;
+      pa.big = big.p;
+      pa.n_big = big.p + 2 * (n_owners / 2 + 1);
+      pa.n_small = n_small;
+      pa.n_chunks = (uint32_t)n_chunks;
+      pa.k = k;
+      pa.p1 = (uint32_t)p1;
+      launch_fill_u64(reinterpret_cast<uint64_t*>(pa.n_big), 1, 0ull, s);
+      launch_own_maps(pa, s);
+      launch_own_part(pa, (uint32_t)n_chunks, 0, s);
+      launch_own_colscan(pa, (uint32_t)n_owners, s);
+      exclusive_scan_u32(start2.p, (int64_t)n_owners + 1, part2.p, s);
+      launch_own_part(pa, (uint32_t)n_chunks, 1, s);
+      HIP_TRY(hipGetLastError());
+    }
     mark(ctx, 3, s);
 
-    // ---- the owners.  Their rows are staged in the level-1 record buffer
-    // (dead once the level-2 scatter has run; rows are far fewer bytes than
+    // ---- the owners.  Their rows are staged in the record buffer that is not
+    // read any more (the level-1 one once the level-2 scatter has run; rows are far fewer bytes than
     // records at any useful coverage), blocks taking chunks of it in turn;
     // if it runs out, the pass runs again with staging of exactly the rows,
     // every owner's at its scanned offset.
     const uint32_t blocks = (uint32_t)std::min<uint64_t>(n_owners, 2ull * ctx->cus);
-    const bool any_big = *std::max_element(nbk.begin(), nbk.end()) > n_small;
+    const bool any_big = fullest > n_small;
     const uint64_t rb = 8ull * W + 4 + 32 + 2;  // key words, count, tallies, codes
     Buf<uint64_t> st_off(pool);
     Buf<uint32_t> st_fixed(pool);
@@ -679,10 +711,10 @@ static int count_owned(kh_ctx* ctx, Packed& pk, const kh_params& p, hipStream_t 
       KH_TRY(st_big.alloc(st_big_bytes));
       stage_in(st_big.p, st_big_bytes);
     } else {
-      stage_in(reinterpret_cast<uint8_t*>(rec1.p), n_rec * R * 8);
+      stage_in(reinterpret_cast<uint8_t*>(flat ? rec2.p : rec1.p), n_rec * R * 8);
     }
-    ca.rec = rec2.p;
-    ca.start2 = start2.p;
+    ca.rec = flat ? rec1.p : rec2.p;
+    ca.start2 = flat ? b1.p : start2.p;
     ca.owner_bucket = owner_bucket.p;
     ca.n_owners = (uint32_t)n_owners;
     ca.k = k;
@@ -714,9 +746,12 @@ static int count_owned(kh_ctx* ctx, Packed& pk, const kh_params& p, hipStream_t 
       if (dbg) launch_fill_u64(reinterpret_cast<uint64_t*>(prof.p), 8, 0ull, s);
       launch_own_count(ca, (uint32_t)ctx->cus, any_big, s);
       HIP_TRY(hipGetLastError());
+      mark(ctx, 5, s);
+      mark(ctx, 6, s);
+      exclusive_scan_u32(row_off.p, (int64_t)n_owners, part2.p, s);
+      mark(ctx, 7, s);
       std::vector<uint64_t> hs((size_t)kOwnStripes * kCtrCount);
-      HIP_TRY(hipMemcpyAsync(hs.data(), stripes.p, hs.size() * 8, hipMemcpyDeviceToHost, s));
-      HIP_TRY(hipStreamSynchronize(s));
+      KH_TRY(fetch(ctx, s, {hs.data(), stripes.p, hs.size() * 8}));
       std::memset(c, 0, sizeof c);
       for (int q = 0; q < kOwnStripes; ++q) {
         const uint64_t* x = &hs[(size_t)q * kCtrCount];
@@ -734,35 +769,32 @@ static int count_owned(kh_ctx* ctx, Packed& pk, const kh_params& p, hipStream_t 
       }
       if (pass > 0 || (c[kCtrStatus] & kStatusProbeLimit) || !(c[kCtrStatus] & kStatusStaging))
         break;
-      // every owner wrote its row count to row_off: scan a copy into the
-      // owners' staging offsets
+      // the owners' row counts, scanned, are their staging offsets
       if (dbg)
         std::fprintf(stderr, "owner k=%u staging of %llu rows ran out: %llu rows\n", k,
                      (unsigned long long)ca.st_cap, (unsigned long long)c[kCtrRows]);
       KH_TRY(st_fixed.alloc(n_owners));
       HIP_TRY(hipMemcpyAsync(st_fixed.p, row_off.p, n_owners * 4, hipMemcpyDeviceToDevice, s));
-      exclusive_scan_u32(st_fixed.p, (int64_t)n_owners, part2.p, s);
       st_big_bytes = c[kCtrRows] * rb + 512;
       KH_TRY(st_big.alloc(st_big_bytes));
       stage_in(st_big.p, st_big_bytes);
       ca.st_fixed = st_fixed.p;
     }
-    mark(ctx, 5, s);
-    mark(ctx, 6, s);
-    exclusive_scan_u32(row_off.p, (int64_t)n_owners, part2.p, s);
-    mark(ctx, 7, s);
     mark(ctx, 8, s);
     mark(ctx, 9, s);
     ctx->last_stats[9] += c[kCtrHeavy];
     ctx->last_stats[11] = c[kCtrWindows];
     if (std::getenv("KMERHIP_OWNER_DEBUG"))
-{ uint32_t nb = 0; (void)hipMemcpy(&nb, pa.n_big, 4, hipMemcpyDeviceToHost);
+{
+      uint32_t nb = 0;
+      if (pa.n_big) (void)hipMemcpy(&nb, pa.n_big, 4, hipMemcpyDeviceToHost);
       std::fprintf(stderr, "owner k=%u: %u owners over %u records\n", k, nb, n_small);
       std::fprintf(stderr, "owner k=%u attempt %d: owners %llu chunks %llu matrix %llu, "
                    "%llu did not fit, largest %llu keys (slots %u), target %.0f records\n",
                    k, attempt, (unsigned long long)n_owners, (unsigned long long)n_chunks,
                    (unsigned long long)m_size, (unsigned long long)c[kCtrHeavy],
-                   (unsigned long long)c[kCtrWindows], slots, target); }
+                   (unsigned long long)c[kCtrWindows], slots, target);
+    }
     if (c[kCtrStatus] & kStatusProbeLimit) {
       if (attempt >= 2) {
         *unfit = true;
@@ -799,6 +831,7 @@ static int count_owned(kh_ctx* ctx, Packed& pk, const kh_params& p, hipStream_t 
     OwnCopyArgs oa{};
     oa.owner_pfx = owner_pfx.p;
     oa.k = k;
+    oa.p1 = (uint32_t)p1;
     oa.st_keys = ca.st_keys;
     oa.st_counts = ca.st_counts;
     oa.st_ext = ca.st_ext;
@@ -1545,6 +1578,12 @@ extern "C" int kh_create(kh_ctx** out, int device, uint64_t hbm_budget_bytes,
     delete ctx;
     return fail(KH_EDEVICE, "event creation failed");
   }
+  // without pinned words results come by copy commands
+  if (hipHostMalloc(reinterpret_cast<void**>(&ctx->box), kBoxWords * 4ull, hipHostMallocDefault) !=
+      hipSuccess) {
+    (void)hipGetLastError();
+    ctx->box = nullptr;
+  }
   for (int i = 0; i < kTimeEvents; ++i) (void)hipEventCreate(&ctx->ev[i]);
   for (int i = 0; i < kMaxK; ++i)
     for (int j = 0; j < 2; ++j) (void)hipEventCreate(&ctx->kev[i][j]);
@@ -1568,6 +1607,7 @@ extern "C" int kh_destroy(kh_ctx* ctx) {
   ctx->live.clear();
   kh_orphan_contigs(ctx);
   if (ctx->graph_exec) (void)hipGraphExecDestroy(ctx->graph_exec);
+  if (ctx->box) (void)hipHostFree(ctx->box);
   (void)hipStreamDestroy(ctx->side);
   (void)hipStreamDestroy(ctx->capture);
   (void)hipEventDestroy(ctx->copy_ev);

@@ -58,12 +58,11 @@ constexpr int kMaxDevices = 64;
 struct DeviceCache {
   std::mutex mu;
   std::multimap<uint64_t, void*> blocks;
-  // Take a kept block of at least `bytes` and at most twice that; its size
-  // goes to *size.
-  void* take(uint64_t bytes, uint64_t* size) {
+  // Take a kept block of `bytes` to `most` bytes; its size goes to *size.
+  void* take(uint64_t bytes, uint64_t most, uint64_t* size) {
     std::lock_guard<std::mutex> lk(mu);
     auto it = blocks.lower_bound(bytes);
-    if (it == blocks.end() || it->first > 2 * bytes + (8ull << 20)) return nullptr;
+    if (it == blocks.end() || it->first > most) return nullptr;
     void* p = it->second;
     *size = it->first;
     blocks.erase(it);
@@ -206,7 +205,12 @@ struct Pool {
                   (unsigned long long)budget);
     void* p = nullptr;
     uint64_t sz = 0;
-    if (void* q = alloc_fn ? nullptr : device_cache(device).take(bytes, &sz)) {
+    // a kept block counts against the budget with its whole size: take none
+    // that is larger than asked for by a good part of it, lest what earlier
+    // contexts left decides whether a call fits
+    uint64_t most = 2 * bytes + (8ull << 20);
+    if (budget) most = std::min(most, bytes + budget / 256);
+    if (void* q = alloc_fn ? nullptr : device_cache(device).take(bytes, most, &sz)) {
       // left by a destroyed context
       if (budget && held + sz > budget) {
         device_cache(device).give(sz, q);  // too big for the budget: allocate
@@ -310,6 +314,7 @@ struct Buf {
 
 enum { kTimeEvents = 12 };  // start/end pairs: pack, Bloom, count, classify, sort, gather
 enum { kMaxK = 8, kStats = 12 };
+constexpr uint32_t kBoxWords = 16384;
 }  // namespace kh
 
 // The C ABI's opaque objects (declared in kmerhip.h at global scope).
@@ -335,6 +340,7 @@ struct kh_ctx {
   hipEvent_t kev[kh::kMaxK][2] = {};     // start/end of each counting pass
   hipGraphExec_t graph_exec = nullptr;   // counting passes of the last call
   int last_graphed = 0;                  // the last batched call replayed it
+  uint32_t* box = nullptr;  // kBoxWords pinned host words (fetch), or null
   kh_tuning tune{};   // free parameters (kh_default_tuning, kh_set_tuning)
   std::unordered_set<kh_contigs*> live_contigs;  // contigs whose data live in `pool`
 };
@@ -385,6 +391,15 @@ namespace kh {
 using RecountFn = std::function<int(HeavyEntry* heavy, uint32_t* index,
                                     uint32_t mask)>;
 int make_table(kh_ctx* ctx, uint32_t k, kh_table** out);
+// Device words (a multiple of four bytes each) to host memory, after all work
+// queued on s: through the context's pinned words, or copy commands where it
+// has none.  Synchronizes s.
+struct Fetch {
+  void* dst;
+  const void* src;
+  uint64_t bytes;
+};
+int fetch(kh_ctx* ctx, hipStream_t s, Fetch a, Fetch b = {}, Fetch c = {});
 // Reads (device) copied in `order` (device read indices) into o_seq, o_qual
 // (offsets[n_reads] bytes) and o_off (n_reads + 1); KH_EINVAL if order is
 // not a permutation.

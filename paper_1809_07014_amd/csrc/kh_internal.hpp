@@ -19,6 +19,8 @@ struct PackArgs {
   uint64_t* bad;
   uint64_t* st;
   int64_t plane_words;
+  int64_t base_words;   // launch_plane_init
+  int inited;           // it has run: the read-start plane is clear
   unsigned long long* ctr;
 };
 
@@ -234,6 +236,7 @@ struct OwnCountArgs {
   const uint64_t* rec;
   const uint32_t* start2;
   const uint16_t* owner_bucket;  // level-1 bucket (top key bits) of each owner
+                                 // (null: the owners are the buckets)
   uint32_t n_owners;
   uint32_t k, p1, min_count, t_min_ext, t_base, err_ppm, use_bloom;
   uint32_t slots;          // a big owner's table slots (<= own_slots(k); a testing hook)
@@ -256,8 +259,8 @@ struct OwnCountArgs {
 };
 
 struct OwnCopyArgs {
-  const uint8_t* owner_pfx;  // key bits each owner's keys share
-  uint32_t k;
+  const uint8_t* owner_pfx;  // key bits each owner's keys share (null: p1)
+  uint32_t k, p1;
   const uint64_t* st_keys;
   const uint32_t* st_counts;
   const uint32_t* st_ext;
@@ -289,7 +292,18 @@ void launch_gather_strided(const uint32_t* src, uint64_t stride, uint32_t n, uin
 
 void launch_fill_u64(uint64_t* p, uint64_t n, uint64_t v, hipStream_t s);
 void launch_reset_ctr(unsigned long long* ctr, uint64_t keep, hipStream_t s);
+// Clear the read-start plane, the words of the others that packing leaves
+// (no base, of no quality, not a base) and the counters, in one launch.
+void launch_plane_init(const PackArgs& a, hipStream_t s);
 void launch_pack(const PackArgs& a, hipStream_t s);
+// Up to three stretches of 32-bit words copied one after another to dst
+// (pinned host memory: results for the host to read after a synchronise).
+struct PostArgs {
+  const uint32_t* src[3];
+  uint32_t words[3];
+  uint32_t* dst;
+};
+void launch_post(const PostArgs& a, hipStream_t s);
 // The two halves of launch_pack: bases, quality and non-base planes of the
 // positions [p0, p1) (p0 a multiple of 64; p1 a multiple of 64 or n), and
 // the read-start plane with the offsets check.

@@ -328,6 +328,7 @@ __global__ __launch_bounds__(kOwnRouteThreads) void k_own_hist(OwnRouteArgs a) {
   lds_barrier();
   for (int i = tid; i < nbins; i += kOwnRouteThreads)
     a.h1[(uint64_t)i * gridDim.x + blockIdx.x] = s_h[i];
+  if (blockIdx.x == 0 && tid == 0) a.h1[(uint64_t)nbins * gridDim.x] = 0;  // the total, scanned
   block_add(&a.ctr[kCtrWindows], nwin, s_red);
 }
 
@@ -1150,7 +1151,7 @@ __global__ __launch_bounds__(SmallShape<R>::kThreads, 4) void k_own_count(OwnCou
       }
       continue;
     }
-    const uint64_t digit = a.owner_bucket[sb];
+    const uint64_t digit = a.owner_bucket ? a.owner_bucket[sb] : sb;
     const int nq = (int)((n + NT - 1) / NT);  // record columns in use (uniform)
     PROF_MARK(0);
     // ---- the records, and free slots
@@ -1390,7 +1391,7 @@ __global__ __launch_bounds__(kOwnCopyThreads) void k_own_copy(OwnCopyArgs a) {
   const uint32_t n = a.rows_sb[sb];
   if (n == 0) return;  // the whole block
   const uint64_t src0 = a.st_off[sb], dst0 = a.row_off[sb];
-  const int pfx = a.owner_pfx[sb];
+  const int pfx = a.owner_pfx ? (int)a.owner_pfx[sb] : (int)a.p1;
   const int rest = 2 * (int)a.k - pfx;
   const int len = rest < 32 ? (rest > 0 ? rest : 0) : 32;  // sort-key bits
   const int nb = len < kOwnSortBits ? len : kOwnSortBits;

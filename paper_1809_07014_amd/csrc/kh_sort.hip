@@ -278,6 +278,10 @@ uint64_t scan_tmp_words(int64_t m) {
 void exclusive_scan_u32(uint32_t* x, int64_t m, uint32_t* part, hipStream_t s) {
   if (m <= 0) return;
   const int64_t np = (m + kScanChunk - 1) / kScanChunk;
+  if (np <= 4) {  // one block scans it all, a few chunks one after another
+    hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(kBlock), 0, s, x, m);
+    return;
+  }
   hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)np), dim3(kBlock), 0, s, x, m, part);
   hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(kBlock), 0, s, part, np);
   hipLaunchKernelGGL(k_scan_down, dim3((unsigned)np), dim3(kBlock), 0, s, x, m, part);
