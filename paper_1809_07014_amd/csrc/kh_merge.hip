@@ -240,8 +240,7 @@ extern "C" int kh_merge_contigs(kh_ctx* ctx, const kh_table* t, const char* seq,
   int64_t total = 0;
   if (n_contigs > 0) {
     if (on_device) {
-      HIP_TRY(hipMemcpyAsync(&total, offsets + n_contigs, 8, hipMemcpyDeviceToHost, s));
-      HIP_TRY(hipStreamSynchronize(s));
+      KH_TRY(fetch(ctx, s, {&total, offsets + n_contigs, 8}));
     } else {
       total = offsets[n_contigs];
     }

@@ -686,8 +686,7 @@ int traverse_ws(kh_ctx* ctx, const kh_table* t, hipStream_t s, kh_contigs* out) 
     HIP_TRY(hipGetLastError());
     exclusive_scan_u32(cnt.p, words + 1, part.p, s);
     uint32_t n_split = 0;
-    HIP_TRY(hipMemcpyAsync(&n_split, cnt.p + words, 4, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    KH_TRY(fetch(ctx, s, {&n_split, cnt.p + words, 4}));
     nq = 2 * (uint64_t)n_split;
     launch_fill_u64(scal.p, 4, 0ull, s);
     launch_fill_u64(reinterpret_cast<uint64_t*>(flags.p), (kMaxRounds + 2) / 2, 0ull, s);
@@ -724,9 +723,7 @@ int traverse_ws(kh_ctx* ctx, const kh_table* t, hipStream_t s, kh_contigs* out) 
     HIP_TRY(hipGetLastError());
     uint32_t moved[kMaxRounds + 2];
     uint64_t placed = 0;
-    HIP_TRY(hipMemcpyAsync(moved, flags.p, sizeof moved, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(&placed, scal.p, 8, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    KH_TRY(fetch(ctx, s, {moved, flags.p, sizeof moved}, {&placed, scal.p, 8}));
     int ran = 0;
     while (ran < rounds && moved[ran]) ++ran;
     out->rounds += ran;
@@ -771,8 +768,7 @@ int traverse_ws(kh_ctx* ctx, const kh_table* t, hipStream_t s, kh_contigs* out) 
   HIP_TRY(hipGetLastError());
   exclusive_scan_u32(rcnt.p, words + 1, part.p, s);
   uint32_t n_contigs = 0;
-  HIP_TRY(hipMemcpyAsync(&n_contigs, rcnt.p + words, 4, hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
+  KH_TRY(fetch(ctx, s, {&n_contigs, rcnt.p + words, 4}));
   const uint64_t nc = n_contigs;
   Buf<uint64_t> lens(pool), offs(pool), depth(pool);
   Buf<int64_t> nk(pool);
@@ -791,8 +787,7 @@ int traverse_ws(kh_ctx* ctx, const kh_table* t, hipStream_t s, kh_contigs* out) 
   KH_TRY(scan_exclusive(pool, lens.p, offs.p, (int64_t)nc, scal.p + 1, s));
   HIP_TRY(hipMemcpyAsync(offs.p + nc, scal.p + 1, 8, hipMemcpyDeviceToDevice, s));
   uint64_t h[4];
-  HIP_TRY(hipMemcpyAsync(h, scal.p, 32, hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
+  KH_TRY(fetch(ctx, s, {h, scal.p, 32}));
   if (h[3]) return fail(KH_EDEVICE, "inconsistent contig chains (code %u)", (unsigned)h[3]);
   const uint64_t total = h[1];
   nodes.reset();
@@ -810,8 +805,7 @@ int traverse_ws(kh_ctx* ctx, const kh_table* t, hipStream_t s, kh_contigs* out) 
                      place.p, nq, total, seq.p, rowc.p, bad);
   HIP_TRY(hipGetLastError());
   unsigned int hbad = 0;
-  HIP_TRY(hipMemcpyAsync(&hbad, bad, 4, hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
+  KH_TRY(fetch(ctx, s, {&hbad, bad, 4}));
   if (hbad) return fail(KH_EDEVICE, "inconsistent contig chains (code %u)", hbad);
   out->cycle_kmers = (int64_t)h[2];
   out->n_contigs = (int64_t)nc;
