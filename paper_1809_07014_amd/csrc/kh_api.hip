@@ -163,9 +163,11 @@ static int finish_pack(kh_ctx* ctx, Packed& pk, hipStream_t s) {
 
 // Upload (if needed) and pack a read set into device bit planes.
 // allow_stream: host reads may be left for the caller to upload in chunks
-// (Packed::packed says how far they are).
+// (Packed::packed says how far they are).  known: the base count of device
+// reads if the caller has read it (else -1).
 static int pack_reads(kh_ctx* ctx, const kh_reads* r, const kh_params& p,
-                      hipStream_t s, Packed& pk, bool allow_stream = false) {
+                      hipStream_t s, Packed& pk, bool allow_stream = false,
+                      int64_t known = -1) {
   if (!r) return fail(KH_EINVAL, "reads is NULL");
   if (r->n_reads < 0) return fail(KH_EINVAL, "n_reads < 0");
   pk.n_reads = r->n_reads;
@@ -173,7 +175,8 @@ static int pack_reads(kh_ctx* ctx, const kh_reads* r, const kh_params& p,
   int64_t n = 0;
   if (r->n_reads > 0) {
     if (r->on_device) {
-      KH_TRY(fetch(ctx, s, {&n, r->offsets + r->n_reads, sizeof n}));
+      n = known;
+      if (known < 0) KH_TRY(fetch(ctx, s, {&n, r->offsets + r->n_reads, sizeof n}));
     } else {
       if (r->offsets[0] != 0) return fail(KH_EINVAL, "offsets[0] must be 0");
       for (int64_t i = 0; i < r->n_reads; ++i)
@@ -416,26 +419,7 @@ int kh::finish_rows(kh_ctx* ctx, unsigned long long* ctr, uint8_t* table,
       return fail(KH_EDEVICE, "row sort failed: %s", hipGetErrorString(hipGetLastError()));
     uint64_t* pfx_sorted = which ? pfx_b.p : pfx_a.p;
     idx_sorted = which ? idx_b.p : idx_a.p;
-    if (2 * k > 64) {
-      launch_fix_ties(pfx_sorted, idx_sorted, rows, table, k, ctr, s);
-      HIP_TRY(hipGetLastError());
-      KH_TRY(fetch(ctx, s, {c, ctr, sizeof c}));
-      if (c[kCtrStatus] & kStatusLongTies) {
-        // many keys share their top 20 bases: sort by the full key instead
-        Buf<uint64_t> ka(pool), kb(pool);
-        KH_TRY(ka.alloc((uint64_t)rows * W));
-        KH_TRY(kb.alloc((uint64_t)rows * W));
-        uint32_t* other = which ? idx_a.p : idx_b.p;
-        launch_row_keys(idx_sorted, rows, table, k, ka.p, s);
-        const int bits0 = 2 * (int)k - 64 * (W - 1);
-        const int w2 = radix_sort(ka.p, idx_sorted, kb.p, other, rows, W, bits0,
-                                  tmp.p, s);
-        HIP_TRY(hipGetLastError());
-        if (w2) idx_sorted = other;
-        HIP_TRY(hipStreamSynchronize(s));
-        ctx->last_stats[11] = 1;  // full-key sort was needed
-      }
-    }
+    if (2 * k > 64) launch_fix_ties(pfx_sorted, idx_sorted, rows, table, k, ctr, s);
     HIP_TRY(hipGetLastError());
   }
   mark(ctx, 9, s);
@@ -466,7 +450,26 @@ int kh::finish_rows(kh_ctx* ctx, unsigned long long* ctr, uint8_t* table,
   launch_gather(ga, s);
   HIP_TRY(hipGetLastError());
   mark(ctx, 11, s);
-  HIP_TRY(hipStreamSynchronize(s));
+  if (rows > 1 && 2 * k > 64) {  // did the order of equal prefixes hold?
+    KH_TRY(fetch(ctx, s, {c, ctr, sizeof c}));
+    if (c[kCtrStatus] & kStatusLongTies) {
+      // many keys share their top 20 bases: sort by the full key instead, and
+      // gather again
+      Buf<uint64_t> ka(pool), kb(pool);
+      KH_TRY(ka.alloc((uint64_t)rows * W));
+      KH_TRY(kb.alloc((uint64_t)rows * W));
+      uint32_t* other = idx_sorted == idx_a.p ? idx_b.p : idx_a.p;
+      launch_row_keys(idx_sorted, rows, table, k, ka.p, s);
+      const int bits0 = 2 * (int)k - 64 * (W - 1);
+      if (radix_sort(ka.p, idx_sorted, kb.p, other, rows, W, bits0, tmp.p, s)) ga.idx = other;
+      launch_gather(ga, s);
+      HIP_TRY(hipGetLastError());
+      HIP_TRY(hipStreamSynchronize(s));
+      ctx->last_stats[11] = 1;  // full-key sort was needed
+    }
+  } else {
+    HIP_TRY(hipStreamSynchronize(s));
+  }
 
   t->n_rows = rows;
   if (!to_caller) {
@@ -1071,9 +1074,9 @@ static int count_packed(kh_ctx* ctx, Packed& pk, const kh_params& p,
 }
 
 int kh::count_into(kh_ctx* ctx, const kh_reads* reads, const kh_params& p, hipStream_t s,
-                   kh_table* t) {
+                   kh_table* t, int64_t n_bases) {
   Packed pk(&ctx->pool);
-  KH_TRY(pack_reads(ctx, reads, p, s, pk, false));
+  KH_TRY(pack_reads(ctx, reads, p, s, pk, false, n_bases));
   return count_packed_into(ctx, pk, p, s, t);
 }
 

@@ -444,8 +444,9 @@ int count_absent(kh_ctx* ctx, const kh_reads* reads, const kh_params& p, const u
                  const RowIndex& ix, hipStream_t s, kh_table* t);
 // Pack a read set and count one k into an existing table object (whose rows
 // may go to the caller's buffers, kh_table::dst_cap); no streamed upload.
+// n_bases: offsets[n_reads] if the caller has read it, else -1.
 int count_into(kh_ctx* ctx, const kh_reads* reads, const kh_params& p, hipStream_t s,
-               kh_table* t);
+               kh_table* t, int64_t n_bases);
 
 }  // namespace kh
 

@@ -110,10 +110,17 @@ __global__ __launch_bounds__(kBlock) void k_pack(
   if (p0 + 16 <= n) {  // any alignment
     __builtin_memcpy(c, seq + p0, 16);
     __builtin_memcpy(q, qual + p0, 16);
-  } else {  // the positions from n on: byte 0, not a base
-    for (int i = 0; p0 + i < n; ++i) {
-      c[i / 4] |= (uint32_t)seq[p0 + i] << (8 * (i % 4));
-      q[i / 4] |= (uint32_t)qual[p0 + i] << (8 * (i % 4));
+  } else {  // the positions from n on: byte 0, not a base; every load at once
+    uint8_t cs[16], qs[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      cs[i] = p0 + i < n ? seq[p0 + i] : (uint8_t)0;
+      qs[i] = p0 + i < n ? qual[p0 + i] : (uint8_t)0;
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      c[i / 4] |= (uint32_t)cs[i] << (8 * (i % 4));
+      q[i / 4] |= (uint32_t)qs[i] << (8 * (i % 4));
     }
   }
   const uint32_t low = (uint32_t)(q_min & 0x7f) * 0x01010101u;

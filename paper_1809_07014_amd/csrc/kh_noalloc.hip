@@ -72,8 +72,8 @@ extern "C" int kh_count_noalloc(const kh_reads* reads, const kh_params* params, 
   std::lock_guard<std::mutex> lk(g_mu[device]);
   uint8_t* base = nullptr;
   KH_TRY(scratch_of(device, &base));
+  int64_t n = -1;
   if (reads->n_reads > 0) {  // the input bound, before anything is launched
-    int64_t n = 0;
     HIP_TRY(hipMemcpyAsync(&n, reads->offsets + reads->n_reads, sizeof n,
                            hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
@@ -102,7 +102,7 @@ extern "C" int kh_count_noalloc(const kh_reads* reads, const kh_params* params, 
   t.dst_ext = ext;
   t.dst_codes = codes;
   t.dst_cap = max_rows;
-  const int rc = count_into(&ctx, reads, *params, s, &t);
+  const int rc = count_into(&ctx, reads, *params, s, &t, n);
   *n_rows = t.n_rows;
   if (n_windows) *n_windows = t.n_windows;
   if (rc != KH_OK) {

@@ -5,6 +5,7 @@
 // counts gives every (digit, block) its output base, (3) each block re-reads
 // its tile and scatters it, ranking equal digits stably with wave ballots.
 // No block ever waits on another, so the sort cannot stall.
+#include <algorithm>
 #include <vector>
 
 #include "kh_internal.hpp"
@@ -336,19 +337,17 @@ static int radix_sort_w(uint64_t* ka, uint32_t* ia, uint64_t* kb, uint32_t* ib,
 // runs of consecutive buckets holding at most kSegCap rows (segments) are
 // each sorted by the remaining bits in LDS by one workgroup.  A row then
 // crosses device memory about three times instead of once per 8-bit digit.
-// A set of at most kSegCap rows is one segment, sorted by one launch.
+// A set of at most kSegCap rows is sorted by one launch of k_rank_sort.
 // A bucket larger than a segment (rare: bucket sizes stay within a few times
 // their mean for k-mer keys) is sorted by the plain LSD passes on its range.
 
 constexpr int kSegThreads = 1024;
 constexpr int kSegWaves = kSegThreads / 64;
-constexpr int kSegCap = 16384;    // rows of a segment (its u64 values: 128 KiB of LDS)
+constexpr int kSegCap = 16384;    // rows of the largest segment (its u64 values: 128 KiB of LDS)
 constexpr int kSegPosBits = 14;   // a row's place in its segment
-constexpr int kSegItems = kSegCap / kSegThreads;
 constexpr int kSegMaxKeyBits = 64 - kSegPosBits;
 constexpr int kSegDigit = 5;      // key bits per LDS pass
 constexpr int kSegBins = 1 << kSegDigit;
-constexpr int kSegCounters = kSegBins * kSegItems * kSegWaves;  // 8,192
 
 struct SortSeg {
   int64_t r0;     // first row
@@ -367,15 +366,22 @@ struct SortSeg {
 // order gives every group its first position, and each value goes to its
 // group's position plus its rank: a stable pass with four barriers.  The
 // values of a pass are held in registers, so one LDS buffer serves as both
-// source and destination.  `segs` null: the one segment `one`.
+// source and destination.
+//
+// A pass costs the same whether a segment is full or not, and a block its
+// longest chain of them, so sets of a few million rows take shorter segments
+// (kSegItems x 1,024 rows; sort_rows picks): 2e6 rows of 40-bit
+// keys take 65 us in segments of 4,096, 117 us in segments of 16,384.
+template <int kSegItems>
 __global__ __launch_bounds__(kSegThreads) void k_seg_sort(
     const uint64_t* __restrict__ kin, const uint32_t* __restrict__ iin,
     uint64_t* __restrict__ kout, uint32_t* __restrict__ iout,
-    const SortSeg* __restrict__ segs, SortSeg one) {
-  __shared__ uint64_t v[kSegCap];
+    const SortSeg* __restrict__ segs) {
+  constexpr int kSegCounters = kSegBins * kSegItems * kSegWaves;
+  __shared__ uint64_t v[kSegItems * kSegThreads];
   __shared__ uint16_t cnt[kSegCounters];
   __shared__ uint32_t s_part[kSegWaves];
-  const SortSeg sg = segs ? segs[blockIdx.x] : one;
+  const SortSeg sg = segs[blockIdx.x];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
   const int n = sg.n;
@@ -451,6 +457,48 @@ __global__ __launch_bounds__(kSegThreads) void k_seg_sort(
   }
 }
 
+// Up to kSegCap rows in one launch: a row's place is the number of rows before
+// it, counted directly.  A block takes 64 rows, one per lane, and holds all
+// rows in LDS; its 16 waves each compare the 64 with a sixteenth of them
+// (broadcast reads, two rows each), and the waves' counts are added.  Rows
+// compare by key, then index, as one word.
+//
+// Bound by the compares (n x n over 64 lanes): 11,500 rows 21 us, from 109 us
+// as one segment sorted by one block.
+__global__ __launch_bounds__(kSegThreads) void k_rank_sort(
+    const uint64_t* __restrict__ kin, const uint32_t* __restrict__ iin,
+    uint64_t* __restrict__ kout, uint32_t* __restrict__ iout, int n) {
+  __shared__ __align__(16) uint64_t v[kSegCap];
+  __shared__ uint32_t s_rank[kSegWaves][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int i = blockIdx.x * 64 + lane;
+  // each wave's share in eights; rows past the last compare greater than any
+  // (keys have at most 50 bits)
+  const int per = (n + 8 * kSegWaves - 1) / (8 * kSegWaves) * 8;
+  for (int j = threadIdx.x; j < per * kSegWaves; j += kSegThreads)
+    v[j] = j < n ? (kin[j] << kSegPosBits) | (uint64_t)j : ~0ull;
+  __syncthreads();
+  const uint64_t me = i < n ? v[i] : 0ull;
+  const ulonglong2* o = reinterpret_cast<const ulonglong2*>(v + wave * per);
+  uint32_t rank = 0;
+  for (int j = 0; j < per / 2; j += 4) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const ulonglong2 x = o[j + e];
+      rank += x.x < me ? 1u : 0u;
+      rank += x.y < me ? 1u : 0u;
+    }
+  }
+  s_rank[wave][lane] = rank;
+  __syncthreads();
+  if (wave != 0 || i >= n) return;
+  uint32_t at = 0;
+#pragma unroll
+  for (int w = 0; w < kSegWaves; ++w) at += s_rank[w][lane];
+  kout[at] = me >> kSegPosBits;
+  iout[at] = iin[i];
+}
+
 // starts[b] = first row of bucket b (rows sorted by their top bits), for
 // the buckets that hold rows; the others keep -1.
 __global__ __launch_bounds__(kBlock) void k_bucket_starts(const uint64_t* __restrict__ keys,
@@ -465,11 +513,14 @@ __global__ __launch_bounds__(kBlock) void k_bucket_starts(const uint64_t* __rest
 // Top bits B of the segmented sort for n > kSegCap rows of `bits`-bit keys
 // (about 2,048 rows per bucket on average), or 0 where the plain LSD sort
 // is used.
+// Finer buckets where they cost no further pass (B up to the next multiple of
+// 8), for shorter segments.
 static int seg_bucket_bits(int64_t n, int bits) {
   if (n <= kSegCap || bits < 16) return 0;
   int B = 1;
   while (B < 16 && ((int64_t)2048 << B) < n) ++B;
   if (B < bits - kSegMaxKeyBits + 4) return 0;  // segments could span too few buckets
+  for (int e = 0; e < 2 && B % 8 != 0 && ((int64_t)512 << B) < n; ++e) ++B;
   return B;
 }
 
@@ -481,10 +532,9 @@ uint64_t seg_sort_bytes(int64_t n, int bits) {
 
 int sort_rows(uint64_t* ka, uint32_t* ia, uint64_t* kb, uint32_t* ib, int64_t n, int bits,
               uint32_t* tmp, void* scratch, hipStream_t s, int* which) {
-  if (n > 1 && n <= kSegCap && bits <= kSegMaxKeyBits) {  // one segment: one launch
-    const SortSeg one{0, (int32_t)n, bits, 0ull};
-    hipLaunchKernelGGL(k_seg_sort, dim3(1), dim3(kSegThreads), 0, s, ka, ia, kb, ib,
-                       (const SortSeg*)nullptr, one);
+  if (n > 1 && n <= kSegCap && bits <= kSegMaxKeyBits) {  // one launch
+    hipLaunchKernelGGL(k_rank_sort, dim3((unsigned)((n + 63) / 64)), dim3(kSegThreads), 0, s, ka,
+                       ia, kb, ib, (int)n);
     *which = 1;
     return hipGetLastError() == hipSuccess ? 0 : 1;
   }
@@ -525,6 +575,12 @@ int sort_rows(uint64_t* ka, uint32_t* ia, uint64_t* kb, uint32_t* ib, int64_t n,
   std::vector<SortSeg> segs;
   std::vector<std::pair<int64_t, int64_t>> big;  // buckets sorted by the LSD passes
   const int span_bits = kSegMaxKeyBits - low;     // buckets per segment: 2^span_bits
+  // the shortest segments that hold the fullest bucket (canonical keys and the
+  // genomes' composition crowd some prefixes)
+  int64_t fullest = 0;
+  for (uint64_t b = 0; b < nbk; ++b) fullest = std::max(fullest, st[b + 1] - st[b]);
+  const int items = fullest <= 4 * kSegThreads ? 4 : fullest <= 8 * kSegThreads ? 8 : 16;
+  const int64_t cap = (int64_t)items * kSegThreads;
   int64_t b0 = -1, last = -1, r0 = 0, cnt = 0;
   auto close = [&]() {
     if (cnt > 0) {
@@ -538,12 +594,12 @@ int sort_rows(uint64_t* ka, uint32_t* ia, uint64_t* kb, uint32_t* ib, int64_t n,
   for (uint64_t b = 0; b < nbk; ++b) {
     const int64_t c = st[b + 1] - st[b];
     if (c == 0) continue;
-    if (c > kSegCap) {
+    if (c > cap) {
       close();
       big.emplace_back(st[b], c);
       continue;
     }
-    if (cnt + c > kSegCap || (b0 >= 0 && ((int64_t)b - b0) >= (1ll << span_bits))) close();
+    if (cnt + c > cap || (b0 >= 0 && ((int64_t)b - b0) >= (1ll << span_bits))) close();
     if (b0 < 0) {
       b0 = (int64_t)b;
       r0 = st[b];
@@ -556,8 +612,14 @@ int sort_rows(uint64_t* ka, uint32_t* ia, uint64_t* kb, uint32_t* ib, int64_t n,
     if (hipMemcpyAsync(dsegs, segs.data(), segs.size() * sizeof(SortSeg),
                        hipMemcpyHostToDevice, s) != hipSuccess)
       return 1;
-    hipLaunchKernelGGL(k_seg_sort, dim3((unsigned)segs.size()), dim3(kSegThreads), 0, s, kx,
-                       ix, ky, iy, (const SortSeg*)dsegs, SortSeg{});
+    const dim3 g((unsigned)segs.size()), t(kSegThreads);
+    const SortSeg* ds = dsegs;
+    if (items == 4)
+      hipLaunchKernelGGL(k_seg_sort<4>, g, t, 0, s, kx, ix, ky, iy, ds);
+    else if (items == 8)
+      hipLaunchKernelGGL(k_seg_sort<8>, g, t, 0, s, kx, ix, ky, iy, ds);
+    else
+      hipLaunchKernelGGL(k_seg_sort<16>, g, t, 0, s, kx, ix, ky, iy, ds);
   }
   for (auto& bg : big) {  // rows of one bucket share its top bits
     const int w = radix_sort(kx + bg.first, ix + bg.first, ky + bg.first, iy + bg.first,
