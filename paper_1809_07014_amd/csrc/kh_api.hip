@@ -599,7 +599,8 @@ static int count_owned(kh_ctx* ctx, Packed& pk, const kh_params& p, hipStream_t 
   // Owners of up to n_small records always fit (k_own_count).  Larger ones
   // (a bucket already split by kOwnL2Max bits, or a prefix its bucket's others
   // are rare beside) take the batched kernel, whose table may be too small for
-  // their keys: then every owner is split by two more bits and counted again.
+  // their keys, in parts too if they are not screened: then every owner is
+  // split by two more bits and counted again.
   // Owners are planned for 0.8 of n_small on average, since the prefixes of
   // one bucket are not equally frequent: 10M reads at k = 21 .. 99 leave 3 to
   // 4 % of the owners over it.
@@ -787,8 +788,7 @@ static int count_owned(kh_ctx* ctx, Packed& pk, const kh_params& p, hipStream_t 
     mark(ctx, 9, s);
     ctx->last_stats[9] += c[kCtrHeavy];
     ctx->last_stats[11] = c[kCtrWindows];
-    if (std::getenv("KMERHIP_OWNER_DEBUG"))
-{
+    if (dbg) {
       uint32_t nb = 0;
       if (pa.n_big) (void)hipMemcpy(&nb, pa.n_big, 4, hipMemcpyDeviceToHost);
       std::fprintf(stderr, "owner k=%u: %u owners over %u records\n", k, nb, n_small);

@@ -686,6 +686,13 @@ int own_slots(uint32_t k) {
 // A and count pass B over the records in batches, 32-bit tallies in an
 // open-addressing table of the keys that pass the screen, then classify
 // (count >= min_count, extension codes) and write the rows to staging.
+//
+// Without the screen every key takes a slot, and an owner of more records than
+// slots may hold too many: its keys are then counted in parts by their hash,
+// pass B and the rows once per part, each part expected to fill the table to
+// 0.86 at most if no key repeats.  (One owner of too many keys had every owner
+// split finer and counted again: 2M reads of 150 bases with 1 % errors, k = 29,
+// 3,544 owners of too many keys, 83.7 ms a call, 11.8 ms in parts.)
 template <int R, int C>
 __global__ __launch_bounds__(kOwnThreads, kOwnThreads * kOwnBlocksPerCU / 256) void k_own_count_big(OwnCountArgs a) {
   constexpr int T = OwnerShape<C>::kSlots;
@@ -752,6 +759,11 @@ __global__ __launch_bounds__(kOwnThreads, kOwnThreads * kOwnBlocksPerCU / 256) v
   PROF_MARK(1);
 
   uint32_t l1 = 0, l2 = 0, passed = 0, claimed = 0;
+  const uint32_t per_part = tcap - tcap / 7;
+  const uint32_t parts =
+      a.use_bloom || tcap < (uint32_t)T || r1 - r0 <= tcap
+          ? 1u
+          : (uint32_t)(r1 - r0 < 8ull * per_part ? (r1 - r0 + per_part - 1) / per_part : 8);
   // Both passes take a lane's records of a batch together, one memory step
   // at a time for all of them (hashes, then every LDS load, then every
   // atomic), so a lane has several LDS round trips in flight instead of one.
@@ -812,6 +824,21 @@ __global__ __launch_bounds__(kOwnThreads, kOwnThreads * kOwnBlocksPerCU / 256) v
     lds_barrier();
   }
   PROF_MARK(2);
+  uint64_t base = 0;          // the owner's first staging row
+  uint32_t done = 0;          // rows of the parts before
+  bool fits = true, unfit = false;  // uniform
+  for (uint32_t part = 0; part < parts; ++part) {
+  if (part > 0) {
+    lds_barrier();  // the last part's rows have left LDS
+    for (int i = tid; i < T; i += kOwnThreads) {
+#pragma unroll
+      for (int c = 0; c < C; ++c) s_ch[c][i] = 0;
+      s_cnt[i] = 0;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) s_tal[e][i] = 0;
+    }
+    lds_barrier();
+  }
   // ---- pass B: count the records whose key completed level 2 (all records
   // without the Bloom screen) in the open-addressing LDS table.  Each stored
   // chunk is written once by CAS from 0 (chunks never are 0), so a slot's
@@ -850,6 +877,11 @@ __global__ __launch_bounds__(kOwnThreads, kOwnThreads * kOwnBlocksPerCU / 256) v
 #pragma unroll
       for (int q = 0; q < NB; ++q)
         if (((uint32_t)(bw[q] >> 32) & pat[q]) != pat[q]) okm &= ~(1u << q);
+    }
+    if (parts > 1) {
+#pragma unroll
+      for (int q = 0; q < NB; ++q)
+        if (__umulhi((uint32_t)h[q] * 0x85ebca6bu, parts) != part) okm &= ~(1u << q);
     }
 #pragma unroll
     for (int q = 0; q < NB; ++q) {  // first word of every record's first probe at once
@@ -899,7 +931,7 @@ __global__ __launch_bounds__(kOwnThreads, kOwnThreads * kOwnBlocksPerCU / 256) v
   // the barrier that completes the table also completes them
   PROF_MARK(3);
   unsigned long long* sc = a.ctr + (uint64_t)(sb % kOwnStripes) * kCtrCount;
-  {
+  if (part + 1 == parts) {
     uint32_t v[4] = {l1, l2, passed, claimed};
 #pragma unroll
     for (int e = 0; e < 4; ++e)
@@ -913,8 +945,8 @@ __global__ __launch_bounds__(kOwnThreads, kOwnThreads * kOwnBlocksPerCU / 256) v
   lds_barrier();
   // s_misc[0] and s_acc change only in the next owner's clear, after a
   // barrier every lane passes after reading them
-  const bool overflow = s_misc[0] != 0;
-  if (tid == 0) {
+  unfit = s_misc[0] != 0;
+  if (tid == 0 && part + 1 == parts) {
     const uint32_t t0 = s_acc[0], t1 = s_acc[1], t2 = s_acc[2], t3 = s_acc[3];
     if (t0) atomicAdd(&sc[kCtrL1New], (unsigned long long)t0);
     if (t1) atomicAdd(&sc[kCtrL2New], (unsigned long long)t1);
@@ -922,19 +954,8 @@ __global__ __launch_bounds__(kOwnThreads, kOwnThreads * kOwnBlocksPerCU / 256) v
     if (t3) atomicAdd(&sc[kCtrClaimed], (unsigned long long)t3);
     // keys of the fullest owner, and the owners whose keys did not fit
     atomicMax(&sc[kCtrWindows], (unsigned long long)t3);
-    if (overflow) {
-      atomicAdd(&sc[kCtrHeavy], 1ull);
-      atomicOr(&sc[kCtrStatus], (unsigned long long)kStatusProbeLimit);
-    }
   }
-  if (overflow) {  // uniform: the flag is stable until the barrier below
-    if (tid == 0) {
-      a.rows_sb[sb] = 0;
-      a.row_off[sb] = 0;
-    }
-    lds_barrier();  // every lane has read the flag and tid 0 the sums
-    continue;
-  }
+  if (unfit) break;  // the flag is stable until the next owner's clear
 
   PROF_MARK(4);
   // ---- classify: a slot is a row when its count reaches min_count.  Rows
@@ -969,6 +990,9 @@ __global__ __launch_bounds__(kOwnThreads, kOwnThreads * kOwnBlocksPerCU / 256) v
 #pragma unroll
   for (int m = 0; m < SP; ++m)  // the kept slots in slot order
     if ((keep >> m) & 1u) s_list[first[m]] = (uint16_t)(tid + m * kOwnThreads);
+  // more rows than one owner of the copy may have
+  unfit = done + rows > (uint32_t)T;
+  if (unfit) break;
   lds_barrier();
   PROF_MARK(6);
   PROF_MARK(7);
@@ -976,22 +1000,28 @@ __global__ __launch_bounds__(kOwnThreads, kOwnThreads * kOwnBlocksPerCU / 256) v
   // rows from a shared cursor (one atomic per chunk, not per owner) and fill
   // them owner after owner; an owner past the end of staging is flagged and
   // the pass runs again with every owner's rows at its scanned offset.
-  uint64_t base;
-  bool fits = true;
-  if (a.st_fixed) {
-    base = a.st_fixed[sb];
-  } else {
-    if (st_cur + rows > st_end) {  // uniform
-      const uint64_t want = rows > a.st_chunk ? rows : a.st_chunk;
-      if (tid == 0) s_chunk = atomicAdd(a.st_cursor, (unsigned long long)want);
-      lds_barrier();
-      st_cur = s_chunk;
-      st_end = st_cur + want;
+  // An owner of several parts takes room for all it may have at its first.
+  if (part == 0) {
+    if (a.st_fixed) {
+      base = a.st_fixed[sb];
+    } else {
+      const uint64_t most = parts == 1 ? rows : (uint64_t)T;
+      if (st_cur + most > st_end) {  // uniform
+        const uint64_t want = most > a.st_chunk ? most : a.st_chunk;
+        if (tid == 0) s_chunk = atomicAdd(a.st_cursor, (unsigned long long)want);
+        lds_barrier();
+        st_cur = s_chunk;
+        st_end = st_cur + want;
+      }
+      base = st_cur;
     }
-    base = st_cur;
-    fits = base + rows <= a.st_cap;
+  }
+  const uint64_t row0 = base + done;
+  if (!a.st_fixed) {
+    fits = row0 + rows <= a.st_cap;
     st_cur += rows;
   }
+  done += rows;
   // the key's level-1 digit goes back above its rest bits
   const uint64_t digit = a.owner_bucket[sb];
   const int rest_bits = own_rest_bits(k), dw = rest_bits >> 6, doff = rest_bits & 63;
@@ -1001,7 +1031,7 @@ __global__ __launch_bounds__(kOwnThreads, kOwnThreads * kOwnBlocksPerCU / 256) v
 #pragma unroll
     for (int c = 0; c < C; ++c) cv[c] = s_ch[c][i];
     from_chunks<R>(cv, ws, f);
-    const uint64_t row = base + j;
+    const uint64_t row = row0 + j;
     uint64_t lw[R + 1];  // the whole key (W <= R + 1 words), least significant first
 #pragma unroll
     for (int q = 0; q <= R; ++q) {
@@ -1027,12 +1057,19 @@ __global__ __launch_bounds__(kOwnThreads, kOwnThreads * kOwnBlocksPerCU / 256) v
         (uint16_t)((uint32_t)side_code(l, cnt, a.t_min_ext, a.t_base, a.err_ppm) |
                    ((uint32_t)side_code(rr, cnt, a.t_min_ext, a.t_base, a.err_ppm) << 8));
   }
+  if (!fits && tid == 0) atomicOr(&sc[kCtrStatus], (unsigned long long)kStatusStaging);
+  }  // parts
   if (tid == 0) {
+    unsigned long long* sc = a.ctr + (uint64_t)(sb % kOwnStripes) * kCtrCount;
+    const uint32_t rows = unfit ? 0u : done;
     a.rows_sb[sb] = rows;
     a.row_off[sb] = rows;
     a.st_off[sb] = base;
     if (rows) atomicAdd(&sc[kCtrRows], (unsigned long long)rows);
-    if (!fits) atomicOr(&sc[kCtrStatus], (unsigned long long)kStatusStaging);
+    if (unfit) {
+      atomicAdd(&sc[kCtrHeavy], 1ull);
+      atomicOr(&sc[kCtrStatus], (unsigned long long)kStatusProbeLimit);
+    }
   }
   lds_barrier();  // the rows have left LDS: the next owner may clear it
   PROF_MARK(8);

@@ -69,6 +69,22 @@ def test_distinct_keys_fill_an_owner(octx, k, extra):
     assert_same_table(st.to_numpy(), oracle.count(reads, k))
 
 
+@pytest.mark.parametrize("k", sorted(RECORDS))
+@pytest.mark.parametrize("times", [1.01, 1.6, 2.5, 6])
+def test_distinct_keys_past_an_owner(octx, k, times):
+    """Without the screen, several times an owner's records of distinct keys
+    (one key beside them many times): counted in parts; at 6 times the parts
+    of short keys do not fit either, which takes the single table."""
+    rng = np.random.default_rng(300 + k)
+    kmers = _one_owner(rng, k, int(times * RECORDS[k]))
+    reads = _reads(kmers + kmers[:40] + kmers[50:51] * 3000, rng)
+    table = octx.count(reads, k, use_bloom=False)
+    st = octx.stats()
+    assert_same_table(table.to_numpy(), oracle.count(reads, k))
+    if times < 6:
+        assert (st["rebuilds"], st["claimed"], st["passed"]) == (0, len(kmers), len(kmers) + 3040)
+
+
 @pytest.mark.parametrize("times", [4096, 65535, 65536, 70000])
 def test_one_key_many_times(octx, times):
     """A homopolymer run: one key `times` times beside others of its owner."""
