@@ -421,8 +421,14 @@ int check_params(const kh_params* p);
 // Index of n sorted rows (n < 2^32 - 1) by their top key bits, in `start`
 // (stream-ordered; kh_rows.hpp).
 struct RowIndex;
+struct MaskedIndex;
 int row_index_build(Pool* pool, const uint64_t* keys, int64_t n, uint32_t k,
                     Buf<uint32_t>& start, RowIndex* ix, hipStream_t s);
+// The same with a digit mask per entry (`start` is its scratch, kept until the
+// stream has passed the build).
+int masked_index_build(Pool* pool, const uint64_t* keys, int64_t n, uint32_t k,
+                       Buf<uint32_t>& start, Buf<uint64_t>& entry, MaskedIndex* ix,
+                       hipStream_t s);
 // Contig windows that are no rows of a table (kh_merge.hip): a bit per window
 // start in `absent` (every word of the tiles is written), the valid windows in
 // ctr[kCtrWindows] and the absent ones in ctr[kCtrPassed].

@@ -43,14 +43,17 @@ __device__ __forceinline__ int base_or_bad(uint8_t c) {
   }
 }
 
-// Bound by the first lines of the reads and three random lines per window
-// looked up (most reads hit with their first).  4e6 reads of 150 bases against
-// 6.2e7 rows: 3.1 ms (15.6 ms with a binary search over all rows per
-// window and a byte load per base).
+// Bound by the first lines of the reads and the random lines of the lookups:
+// most reads hit with their first window, but one without a hit looks up a
+// hundred and more, each by its index line and, where the masks cannot tell,
+// a line or two of rows.  4e6 reads of 150 bases against 6.2e7 rows:
+// 2.4 ms (3.1 ms without the masks, 15.6 ms with a binary search over all rows
+// per window and a byte load per base).  Several windows at a time, by one
+// thread or by sixteen, are slower: they look up windows past the first hit.
 template <int W>
 __global__ __launch_bounds__(kLB) void k_anchor(const uint8_t* seq, const int64_t* offsets,
                                                 int64_t n_reads, uint32_t k,
-                                                const uint64_t* keys, RowIndex ix,
+                                                const uint64_t* keys, MaskedIndex ix,
                                                 const uint32_t* row_contig, uint32_t none,
                                                 uint64_t* key_out, uint32_t* idx_out) {
   const int64_t r = (int64_t)blockIdx.x * kLB + threadIdx.x;
@@ -150,8 +153,9 @@ int localize_w(kh_ctx* ctx, const kh_table* t, const kh_contigs* c, const uint8_
   KH_TRY(tmp.alloc(sort_tmp_words(n)));
   const uint32_t none = (uint32_t)c->n_contigs;
   Buf<uint32_t> start(pool);
-  RowIndex ix{};
-  KH_TRY(row_index_build(pool, t->keys, t->n_rows, t->k, start, &ix, s));
+  Buf<uint64_t> entry(pool);
+  MaskedIndex ix{};
+  KH_TRY(masked_index_build(pool, t->keys, t->n_rows, t->k, start, entry, &ix, s));
   hipLaunchKernelGGL((k_anchor<W>), dim3(lgrid(n)), dim3(kLB), 0, s, seq, offs, n, c->k,
                      t->keys, ix, c->row_contig, none, ka.p, ia.p);
   HIP_TRY(hipGetLastError());

@@ -38,6 +38,23 @@ __global__ __launch_bounds__(kXB) void k_row_index(const uint64_t* keys, int64_t
   }
 }
 
+// Entry p with the digits its rows have; all of them for a bucket of more rows
+// than a thread should look through.
+constexpr uint32_t kMaskRows = 64;
+
+template <int W>
+__global__ __launch_bounds__(kXB) void k_row_masks(const uint64_t* keys, int top, RowIndex ix,
+                                                   int sub, uint2* entry) {
+  const uint64_t p = (uint64_t)blockIdx.x * kXB + threadIdx.x;
+  if (p > 1ull << ix.bits) return;
+  const uint32_t r0 = ix.start[p], r1 = p < 1ull << ix.bits ? ix.start[p + 1] : r0;
+  uint32_t m = r1 - r0 > kMaskRows ? ~0u : 0u;
+  if (!m)
+    for (uint32_t r = r0; r < r1; ++r)
+      m |= 1u << (row_prefix<W>(keys + (uint64_t)r * W, top, ix.bits + sub) & ((1u << sub) - 1u));
+  entry[p] = make_uint2(r0, m);
+}
+
 }  // namespace
 
 // A quarter to half an entry per row: a bucket holds two to four rows where
@@ -62,5 +79,34 @@ int kh::row_index_build(Pool* pool, const uint64_t* keys, int64_t n, uint32_t k,
   HIP_TRY(hipGetLastError());
   ix->start = start.p;
   ix->bits = bits;
+  return KH_OK;
+}
+
+// The masks cost one more pass over the keys (0.28 ms for 6.2e7 rows), which
+// pays where many keys looked up are no rows: the lookups of 4e6 reads
+// localised take 2.4 ms with masks, 3.1 without.  The traversal's and the
+// merge's keys nearly all are rows.
+int kh::masked_index_build(Pool* pool, const uint64_t* keys, int64_t n, uint32_t k,
+                           Buf<uint32_t>& start, Buf<uint64_t>& entry, MaskedIndex* ix,
+                           hipStream_t s) {
+  RowIndex x{};
+  KH_TRY(row_index_build(pool, keys, n, k, start, &x, s));
+  const int room = (2 * (int)k < 32 ? 2 * (int)k : 32) - x.bits;
+  const int sub = room < 5 ? room : 5;
+  entry.pool = pool;
+  KH_TRY(entry.alloc((1ull << x.bits) + 1));
+  uint2* e = reinterpret_cast<uint2*>(entry.p);
+  const int W = (int)(k + 31) / 32, top = 2 * (int)k - 64 * (W - 1);
+  const dim3 g((unsigned)(((1ull << x.bits) + kXB) / kXB)), t(kXB);
+  switch (W) {
+    case 1: hipLaunchKernelGGL(k_row_masks<1>, g, t, 0, s, keys, top, x, sub, e); break;
+    case 2: hipLaunchKernelGGL(k_row_masks<2>, g, t, 0, s, keys, top, x, sub, e); break;
+    case 3: hipLaunchKernelGGL(k_row_masks<3>, g, t, 0, s, keys, top, x, sub, e); break;
+    default: hipLaunchKernelGGL(k_row_masks<4>, g, t, 0, s, keys, top, x, sub, e); break;
+  }
+  HIP_TRY(hipGetLastError());
+  ix->entry = e;
+  ix->bits = x.bits;
+  ix->sub = sub;
   return KH_OK;
 }

@@ -91,4 +91,35 @@ __device__ __forceinline__ int64_t find_row(const uint64_t* keys, const RowIndex
   return -1;
 }
 
+// The index with, beside each entry's first row, a bit per next key digit
+// (`sub` more bits, up to 32 digits) that some row of the bucket has: a key
+// that is no row is told so by the entry's line alone, mostly.
+struct MaskedIndex {
+  const uint2* entry;  // (first row, digits), 2^bits + 1 of them
+  int bits, sub;       // bits + sub <= 32 and 2k
+};
+
+template <int W>
+__device__ __forceinline__ int64_t find_row(const uint64_t* keys, const MaskedIndex& ix, int top,
+                                            const uint64_t (&q)[W]) {
+  const uint32_t p = row_prefix<W>(q, top, ix.bits + ix.sub);
+  const uint64_t b = p >> ix.sub;
+  const uint2 x = ix.entry[b];
+  int64_t lo = x.x, hi = ix.entry[b + 1].x;
+  if (!((x.y >> (p & ((1u << ix.sub) - 1u))) & 1u)) return -1;
+  while (lo < hi) {
+    const int64_t mid = lo + (hi - lo) / 2;
+    uint64_t w[W];
+#pragma unroll
+    for (int j = 0; j < W; ++j) w[j] = keys[mid * W + j];
+    const int c = cmp_rows<W>(w, q);
+    if (c == 0) return mid;
+    if (c < 0)
+      lo = mid + 1;
+    else
+      hi = mid;
+  }
+  return -1;
+}
+
 }  // namespace kh
