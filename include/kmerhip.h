@@ -225,8 +225,8 @@ int kh_heavy_hitters(const kh_table *t, uint32_t min_count, void *stream,
  * [0] pack, [1] Bloom pass, [2] count pass, [3] classify + compact,
  * [4] sort, [5] gather.  With the owner-partitioned count (kh_tuning
  * partitioned = 1): [1] routing of the windows to their owners (both
- * partition passes), [2] the owner pass (Bloom screen, count and classify
- * in LDS), [3] 0, [4] the row-offset scan, [5] the copy of the owners' rows
+ * partition passes), [2] the owner pass (screen, count and classify in
+ * LDS), [3] 0, [4] the row-offset scan, [5] the copy of the owners' rows
  * into the table, sorted by key within each owner.  Filled only when timing
  * is enabled. */
 int kh_set_timing(kh_ctx *ctx, int enable);
@@ -239,11 +239,13 @@ int kh_last_timing(const kh_ctx *ctx, float ms[6]);
  * bytes, [8] windows counted into the table (after the Bloom screen),
  * [9] heavy k-mers recounted, [10] k, [11] 1 if rows needed the full-key
  * sort (many keys sharing their top 20 bases), else 0.  With the
- * owner-partitioned count: [0] owners x LDS slots, [1] keys the owners
- * inserted, [6] finer re-splits after an owner's keys did not fit, [7] bytes
+ * owner-partitioned count: [0] owners x LDS slots of the largest owners, [1]
+ * keys the owners hold (with the Bloom screen those seen at least twice), [2]
+ * their keys (beyond an owner's usual size, the screen's first sightings),
+ * [6] finer re-splits after an owner's keys did not fit, [7] bytes
  * of the routed records and the owners' staging rows, [9] owners whose keys
  * did not fit their table (over every split tried), [11] keys of the
- * fullest owner (counts are exact 32-bit LDS counters: no heavy recount). */
+ * fullest owner (counts are exact in LDS: no heavy recount). */
 int kh_last_stats(const kh_ctx *ctx, uint64_t out[12]);
 
 /* *graphed = 1 if the context's most recent batched kh_count_multi_k call
@@ -425,8 +427,8 @@ typedef struct {
   uint32_t partitioned;      /* 1: kh_count and kh_count_multi_k route each
                                 window to the owner of its key prefix (two
                                 streaming partition passes), every owner
-                                workgroup runs the Bloom screen, the count
-                                and classify in LDS (Section II-B's
+                                workgroup runs the screen, the count and
+                                classify in LDS (Section II-B's
                                 owner-computes layout), and the copy into
                                 the table sorts each owner's rows; k after
                                 k, no device hash table.  0: one open-addressing table in
@@ -434,7 +436,8 @@ typedef struct {
                                 owners' keys do not fit their LDS tables
                                 even after two finer splits, or whose two
                                 record buffers (16 x ceil((2k - min(10, 2k)
-                                + 6) / 64) bytes per window) the HBM budget
+                                + 6) / 64) bytes per window) and three bit
+                                planes (3/8 byte per base) the HBM budget
                                 refuses,
                                 is counted with 0.  Not used by
                                 kh_count_noalloc, with aggregate = 1, or by

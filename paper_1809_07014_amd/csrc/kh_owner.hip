@@ -11,10 +11,12 @@
 // bits into owners of a few thousand records (p2_b chosen per bucket from its
 // size).  Every pass writes contiguous runs at offsets from a scanned
 // histogram matrix, so no device-scope atomic touches a random address.  An
-// owner workgroup then runs Bloom pass A and count pass B over its records in
-// LDS and classifies the kept k-mers; the copy of the owners' rows into the
-// table sorts each owner's rows, and the owners' prefixes are disjoint and in
-// key order, so sorting within owners orders the whole table.
+// owner workgroup then counts its records in LDS, where the keys seen once are
+// told apart exactly (the few owners of too many records for that run Bloom
+// pass A and count pass B), and classifies the kept k-mers; the copy of the
+// owners' rows into the table sorts each owner's rows, and the owners'
+// prefixes are disjoint and in key order, so sorting within owners orders the
+// whole table.
 //
 // A record is one window: its canonical key without the level-1 digit (the
 // bucket implies those bits), shifted left by 6 bits with the extension byte
