@@ -423,7 +423,7 @@ int check_params(const kh_params* p);
 struct RowIndex;
 struct MaskedIndex;
 int row_index_build(Pool* pool, const uint64_t* keys, int64_t n, uint32_t k,
-                    Buf<uint32_t>& start, RowIndex* ix, hipStream_t s);
+                    Buf<uint32_t>& start, RowIndex* ix, hipStream_t s, int most_bits = 32);
 // The same with a digit mask per entry (`start` is its scratch, kept until the
 // stream has passed the build).
 int masked_index_build(Pool* pool, const uint64_t* keys, int64_t n, uint32_t k,

@@ -62,12 +62,17 @@ __global__ __launch_bounds__(kXB) void k_row_masks(const uint64_t* keys, int top
 // two, and the index is small enough that part of it stays in the memory-side
 // cache.  1.6e8 rows (k_link, 1.6e8 lookups): 12.0 ms at ceil(log2 n) bits,
 // 11.6 with one bit less, 11.3 with two; the build 1.6, 1.2 and 1.0 ms.
+// Where there is no memory for that many entries, fewer do (longer searches).
 int kh::row_index_build(Pool* pool, const uint64_t* keys, int64_t n, uint32_t k,
-                        Buf<uint32_t>& start, RowIndex* ix, hipStream_t s) {
+                        Buf<uint32_t>& start, RowIndex* ix, hipStream_t s, int most_bits) {
   int bits = 1;
-  while (bits < 32 && bits < 2 * (int)k && (4ll << bits) < n) ++bits;
+  while (bits < most_bits && bits < 2 * (int)k && (4ll << bits) < n) ++bits;
   start.pool = pool;
-  KH_TRY(start.alloc((1ull << bits) + 1));
+  for (;; bits = bits > 4 ? bits - 3 : 1) {
+    const int rc = start.alloc((1ull << bits) + 1);
+    if (rc == KH_OK) break;
+    if (rc != KH_ENOMEM || bits == 1) return rc;
+  }
   const int W = (int)(k + 31) / 32, top = 2 * (int)k - 64 * (W - 1);
   const dim3 g((unsigned)((n + 1 + kXB - 1) / kXB)), t(kXB);
   switch (W) {
@@ -90,11 +95,15 @@ int kh::masked_index_build(Pool* pool, const uint64_t* keys, int64_t n, uint32_t
                            Buf<uint32_t>& start, Buf<uint64_t>& entry, MaskedIndex* ix,
                            hipStream_t s) {
   RowIndex x{};
-  KH_TRY(row_index_build(pool, keys, n, k, start, &x, s));
+  entry.pool = pool;
+  for (int most = 32;; most = x.bits > 4 ? x.bits - 3 : 1) {
+    KH_TRY(row_index_build(pool, keys, n, k, start, &x, s, most));
+    const int rc = entry.alloc((1ull << x.bits) + 1);
+    if (rc == KH_OK) break;
+    if (rc != KH_ENOMEM || x.bits == 1) return rc;
+  }
   const int room = (2 * (int)k < 32 ? 2 * (int)k : 32) - x.bits;
   const int sub = room < 5 ? room : 5;
-  entry.pool = pool;
-  KH_TRY(entry.alloc((1ull << x.bits) + 1));
   uint2* e = reinterpret_cast<uint2*>(entry.p);
   const int W = (int)(k + 31) / 32, top = 2 * (int)k - 64 * (W - 1);
   const dim3 g((unsigned)(((1ull << x.bits) + kXB) / kXB)), t(kXB);

@@ -46,3 +46,36 @@ def test_first_hit(kh, lctx, k, crowded):
     np.testing.assert_array_equal(got.cpu().numpy(), want)
     contigs.free()
     table.free()
+
+
+@pytest.mark.parametrize("room", [1 << 20, 64 << 10])
+def test_smaller_index(kh, room):
+    """No block of `room` bytes or more to be had, fewer than the index of these
+    rows takes: the same order by longer searches."""
+    import torch
+    limit = [1 << 40]
+
+    def alloc(nbytes, device):
+        return torch.cuda.caching_allocator_alloc(nbytes, device) if nbytes < limit[0] else 0
+
+    def free(ptr, nbytes, device):
+        torch.cuda.caching_allocator_delete(ptr)
+
+    ctx = kh.Context(0, allocator=(alloc, free))
+    try:
+        reads = synth.config(2, scale=0.01)
+        table = ctx.count(reads, 21)
+        contigs = ctx.traverse(table)
+        few = synth.Reads.from_strings(reads.strings()[:500])
+        want = oracle.localize(few, contigs.to_python()["seqs"], 21)
+        dev = kh.DeviceReads.from_host(few)
+        assert table.info()["n_rows"] > room
+        ctx.trim()
+        limit[0] = room
+        got = ctx.localize_order(table, contigs, dev)
+        np.testing.assert_array_equal(got.cpu().numpy(), want)
+        limit[0] = 1 << 40
+        contigs.free()
+        table.free()
+    finally:
+        ctx.close()
