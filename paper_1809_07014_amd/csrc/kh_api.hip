@@ -699,7 +699,6 @@ static int count_owned(kh_ctx* ctx, Packed& pk, const kh_params& p, hipStream_t 
     auto stage_in = [&](uint8_t* p, uint64_t bytes) {
       const uint64_t cap = bytes > 256 ? (bytes - 256) / rb : 0;
       ca.st_cap = cap;
-      ca.st_chunk = std::max<uint64_t>(64, cap / (16ull * blocks));
       ca.st_keys = reinterpret_cast<uint64_t*>(p);
       uint8_t* q = p + (cap * 8 * W + 15) / 16 * 16;
       ca.st_counts = reinterpret_cast<uint32_t*>(q);

@@ -248,7 +248,6 @@ struct OwnCountArgs {
   uint32_t* st_ext;
   uint8_t* st_codes;
   uint64_t st_cap;
-  uint64_t st_chunk;       // staging rows a block takes from the cursor at a time
   unsigned long long* st_cursor;  // next untaken staging row (zero at launch)
   const uint32_t* st_fixed;  // nullptr, or every owner's first staging row
   uint64_t* st_off;        // first staging row of each owner

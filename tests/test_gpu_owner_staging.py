@@ -1,0 +1,56 @@
+"""The owner pass stages its rows in a record buffer it has read: the smallest
+read sets, and sets whose rows fill three quarters of it, fit at the first
+attempt (a second pass over every owner takes a staging buffer of its own,
+which the table's bytes then show); the rows are those of the single table."""
+import pytest
+
+from brute import assert_same_table
+
+pytestmark = pytest.mark.gpu
+
+RECORD_WORDS = {21: 1, 55: 2, 77: 3, 99: 4}
+
+
+@pytest.fixture(scope="module")
+def octx(kh):
+    c = kh.Context(0)
+    assert c.tuning()["partitioned"] == 1
+    yield c
+    c.close()
+
+
+@pytest.fixture(scope="module")
+def sctx(kh):
+    c = kh.Context(0)
+    c.set_tuning(partitioned=0)
+    yield c
+    c.close()
+
+
+def _reads(kh, n, cover):
+    """n reads of 150 bases from a random genome they cover `cover` times."""
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    length = int(n * 150 / cover)
+    letters = torch.tensor([65, 67, 71, 84], dtype=torch.uint8, device="cuda")
+    genome = letters[torch.randint(0, 4, (length,), generator=g, device="cuda")]
+    at = torch.randint(0, length - 149, (n,), generator=g, device="cuda")
+    seq = genome[at[:, None] + torch.arange(150, device="cuda")].reshape(-1).contiguous()
+    return kh.DeviceReads(seq, torch.full_like(seq, 73),
+                          torch.arange(n + 1, device="cuda") * 150)
+
+
+@pytest.mark.parametrize("bloom", [False, True])
+@pytest.mark.parametrize("k", sorted(RECORD_WORDS))
+@pytest.mark.parametrize("n,cover", [(20, 12), (300, 20), (800, 20), (1400, 20),
+                                     (200_000, 12), (200_000, 9)])
+def test_rows_fit_staging(kh, octx, sctx, n, cover, k, bloom):
+    reads = _reads(kh, n, cover)
+    table = octx.count(reads, k, use_bloom=bloom)
+    records = 16 * RECORD_WORDS[k] * table.info()["n_windows"]  # two buffers
+    assert octx.stats()["table_bytes"] == records
+    want = sctx.count(reads, k, use_bloom=False)
+    assert_same_table(table.to_numpy(), want.to_numpy())
+    table.free()
+    want.free()
