@@ -686,7 +686,6 @@ static int count_owned(kh_ctx* ctx, Packed& pk, const kh_params& p, hipStream_t 
     // records at any useful coverage), blocks taking chunks of it in turn;
     // if it runs out, the pass runs again with staging of exactly the rows,
     // every owner's at its scanned offset.
-    const uint32_t blocks = (uint32_t)std::min<uint64_t>(n_owners, 2ull * ctx->cus);
     const bool any_big = fullest > n_small;
     const uint64_t rb = 8ull * W + 4 + 32 + 2;  // key words, count, tallies, codes
     Buf<uint64_t> st_off(pool);
@@ -708,9 +707,13 @@ static int count_owned(kh_ctx* ctx, Packed& pk, const kh_params& p, hipStream_t 
     };
     if (p.min_count <= 1 && n_rec * rb > n_rec * R * 8) {
       // every key is a row, and rows take more bytes than records: stage
-      // them in a buffer of their own, sized for a row per window plus what
-      // the blocks' partly filled staging chunks leave unused
-      st_big_bytes = (n_rec + n_rec / 8 + 20ull * blocks * (uint64_t)own_small_records(k)) * rb + 512;
+      // them in a buffer of their own, with room for a row per window and for
+      // what the blocks' chunks leave unused (a simulation of staging_want,
+      // every window a row: a fifth at 10,000 to 20,000 owners, 6 % at
+      // 140,000).  With room for 20 full owners per block instead, 1,000
+      // reads took 2 GB at k = 21.
+      const uint64_t spare = std::min<uint64_t>(n_rec / 4, n_rec / 8 + (4 << 20));
+      st_big_bytes = (n_rec + spare) * rb + 512;
       KH_TRY(st_big.alloc(st_big_bytes));
       stage_in(st_big.p, st_big_bytes);
     } else {

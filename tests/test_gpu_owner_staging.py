@@ -1,7 +1,10 @@
-"""The owner pass stages its rows in a record buffer it has read: the smallest
+"""Room for the owner pass's rows.
+
+The owner pass stages its rows in a record buffer it has read: the smallest
 read sets, and sets whose rows fill three quarters of it, fit at the first
 attempt (a second pass over every owner takes a staging buffer of its own,
-which the table's bytes then show); the rows are those of the single table."""
+which the table's bytes then show); the rows are those of the single table.
+With min_count 1 the rows have a buffer of their own, sized by the windows."""
 import pytest
 
 from brute import assert_same_table
@@ -54,3 +57,25 @@ def test_rows_fit_staging(kh, octx, sctx, n, cover, k, bloom):
     assert_same_table(table.to_numpy(), want.to_numpy())
     table.free()
     want.free()
+
+
+@pytest.mark.parametrize("k", sorted(RECORD_WORDS))
+@pytest.mark.parametrize("n,cover", [(20, 4), (1000, 4), (30_000, 0.2), (200_000, 0.2)])
+def test_every_window_a_row(kh, sctx, n, cover, k):
+    """min_count 1 in a context whose budget holds the records (two buffers), a
+    quarter more rows than windows, the table itself, and 64 MiB for the rest."""
+    reads = _reads(kh, n, cover)
+    row = 8 * ((k + 31) // 32) + 38
+    windows = n * (151 - k)
+    most = 16 * RECORD_WORDS[k] * windows + windows * 5 // 4 * row + 512
+    ctx = kh.Context(0, hbm_budget=most + windows * row + (64 << 20))
+    try:
+        table = ctx.count(reads, k, min_count=1)
+        st = ctx.stats()  # the owner path's statistics: two record buffers and the staging
+        assert most - 64 * row <= st["table_bytes"] <= most
+        want = sctx.count(reads, k, min_count=1)
+        assert_same_table(table.to_numpy(), want.to_numpy())
+        table.free()
+        want.free()
+    finally:
+        ctx.close()
