@@ -717,6 +717,16 @@ __device__ __forceinline__ uint64_t staging_want(const OwnCountArgs& a, uint64_t
 // 0.86 at most if no key repeats.  (One owner of too many keys had every owner
 // split finer and counted again: 2M reads of 150 bases with 1 % errors, k = 29,
 // 3,544 owners of too many keys, 83.7 ms a call, 11.8 ms in parts.)
+//
+// Few keys many times need no parts, and every part reads all records again:
+// an owner is tried whole first where the block's last one would have fitted
+// whole, or where it has more records than its parts are sure to hold.  A try
+// that fails is cut short (kTryProbes).  500,000 reads of 150 bases, a fifth of
+// them of period 1 or 3, unscreened, k = 21: 47.9 ms a call in parts alone,
+// 13.4 with tries; 100,000 reads with 3 % errors, whose keys fill the parts, 0.49
+// either way.
+constexpr uint32_t kTryProbes = 64;
+
 template <int R, int C>
 __global__ __launch_bounds__(kOwnThreads, kOwnThreads * kOwnBlocksPerCU / 256) void k_own_count_big(OwnCountArgs a) {
   constexpr int T = OwnerShape<C>::kSlots;
@@ -750,6 +760,7 @@ __global__ __launch_bounds__(kOwnThreads, kOwnThreads * kOwnBlocksPerCU / 256) v
   }
 
   // Persistent blocks: the listed owners blockIdx.x, + G, ...
+  bool whole = false;  // the block's last unscreened owner would have fitted whole
   // the block's staging chunk (uniform): empty, behind the small owners' ones
   if (tid == 0)
     s_chunk = __hip_atomic_load(a.st_cursor, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -788,10 +799,11 @@ __global__ __launch_bounds__(kOwnThreads, kOwnThreads * kOwnBlocksPerCU / 256) v
 
   uint32_t l1 = 0, l2 = 0, passed = 0, claimed = 0;
   const uint32_t per_part = tcap - tcap / 7;
-  const uint32_t parts =
+  const uint32_t most_parts =
       a.use_bloom || tcap < (uint32_t)T || r1 - r0 <= tcap
           ? 1u
           : (uint32_t)(r1 - r0 < 8ull * per_part ? (r1 - r0 + per_part - 1) / per_part : 8);
+  uint32_t parts = whole || r1 - r0 > 8ull * per_part ? 1u : most_parts;
   // Both passes take a lane's records of a batch together, one memory step
   // at a time for all of them (hashes, then every LDS load, then every
   // atomic), so a lane has several LDS round trips in flight instead of one.
@@ -855,9 +867,15 @@ __global__ __launch_bounds__(kOwnThreads, kOwnThreads * kOwnBlocksPerCU / 256) v
   uint64_t base = 0;          // the owner's first staging row
   uint32_t done = 0;          // rows of the parts before
   bool fits = true, unfit = false;  // uniform
+  bool again = false;  // the owner did not fit whole
   for (uint32_t part = 0; part < parts; ++part) {
-  if (part > 0) {
-    lds_barrier();  // the last part's rows have left LDS
+  if (part > 0 || again) {
+    lds_barrier();  // the last part's rows have left LDS (or every lane has read the flag)
+    if (tid == 0) {
+      s_misc[0] = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s_acc[e] = 0;
+    }
     for (int i = tid; i < T; i += kOwnThreads) {
 #pragma unroll
       for (int c = 0; c < C; ++c) s_ch[c][i] = 0;
@@ -875,7 +893,10 @@ __global__ __launch_bounds__(kOwnThreads, kOwnThreads * kOwnBlocksPerCU / 256) v
   // non-zero word is final).  An occurrence adds 1 to its left tally (or to the no-left-extension count)
   // and 1 to its right tally if it has one: the count is the sum of the
   // first five, so it needs no add of its own.
+  const bool trying = parts < most_parts;
+  const uint32_t probes = trying ? kTryProbes : tcap;
   for (uint64_t b0 = r0; b0 < r1; b0 += kBatch) {
+    if (trying && *static_cast<volatile uint32_t*>(&s_misc[0])) break;  // no barrier inside
     const int nq = lane_records<NB>(b0, r1, tid);
     uint32_t okm = (1u << nq) - 1u;  // bit q: record q is counted
     uint64_t ch[NB][C], w0[NB], h[NB];
@@ -923,7 +944,7 @@ __global__ __launch_bounds__(kOwnThreads, kOwnThreads * kOwnBlocksPerCU / 256) v
       if (!((okm >> q) & 1u)) continue;
       ++passed;
       uint32_t i = i0[q];
-      for (uint32_t probe = 0; probe < tcap; ++probe) {
+      for (uint32_t probe = 0; probe < probes; ++probe) {
         bool match = true;
 #pragma unroll
         for (int c = 0; c < C; ++c) {
@@ -944,7 +965,7 @@ __global__ __launch_bounds__(kOwnThreads, kOwnThreads * kOwnBlocksPerCU / 256) v
         }
         if (++i == tcap) i = 0;
       }
-      if (slot[q] < 0) s_misc[0] = 1;  // the owner's keys do not fit: split finer
+      if (slot[q] < 0) s_misc[0] = 1;  // the owner's keys do not fit
     }
 #pragma unroll
     for (int q = 0; q < NB; ++q) {
@@ -971,9 +992,18 @@ __global__ __launch_bounds__(kOwnThreads, kOwnThreads * kOwnBlocksPerCU / 256) v
     }
   }
   lds_barrier();
-  // s_misc[0] and s_acc change only in the next owner's clear, after a
-  // barrier every lane passes after reading them
+  // s_misc[0] and s_acc change only in the next clear, after a barrier every
+  // lane passes after reading them
   unfit = s_misc[0] != 0;
+  if (unfit && trying) {
+    unfit = whole = false;
+    again = true;
+    parts = most_parts;
+    passed = claimed = 0;
+    part = ~0u;  // from part 0
+    continue;
+  }
+  if (most_parts > 1 && part + 1 == parts) whole = s_acc[3] <= tcap / 4 * 3;
   if (tid == 0 && part + 1 == parts) {
     const uint32_t t0 = s_acc[0], t1 = s_acc[1], t2 = s_acc[2], t3 = s_acc[3];
     if (t0) atomicAdd(&sc[kCtrL1New], (unsigned long long)t0);
