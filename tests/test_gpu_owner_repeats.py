@@ -1,8 +1,7 @@
 """Owners of very many records of few keys (runs of one base, tandem repeats, a
 small genome sequenced thousands of times over), unscreened: the rows are those
 of the screened count and of the oracle, and the call takes no longer than the
-screened one by much (counting every such owner in parts took three times as
-long)."""
+screened one by much (1.5 times, with every such owner counted in parts)."""
 import time
 
 import numpy as np
@@ -72,7 +71,7 @@ def test_repeated_and_distinct_owners(octx, times):
 
 def test_repeats_take_no_parts(kh, octx):
     import torch
-    seq, off = _reads(200_000, 80_000)
+    seq, off = _reads(500_000, 100_000)
     seq = torch.from_numpy(seq).cuda()
     reads = kh.DeviceReads(seq, torch.full_like(seq, 73), torch.from_numpy(off).cuda())
 
@@ -85,4 +84,4 @@ def test_repeats_take_no_parts(kh, octx):
             times.append(time.perf_counter() - t0)
         return min(times)
 
-    assert best(False) < 1.6 * best(True)
+    assert best(False) < 1.2 * best(True)
