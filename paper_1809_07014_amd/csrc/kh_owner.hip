@@ -1055,12 +1055,13 @@ __global__ __launch_bounds__(kOwnThreads, kOwnThreads * kOwnBlocksPerCU / 256) v
   PROF_MARK(6);
   PROF_MARK(7);
   // ---- rows to staging (staging_want).  An owner of several parts takes room
-  // for all it may have at its first.
+  // for all of them at its first: as many rows each, and a quarter more.
   if (part == 0) {
     if (a.st_fixed) {
       base = a.st_fixed[sb];
     } else {
-      const uint64_t most = parts == 1 ? rows : (uint64_t)T;
+      const uint32_t all = rows * parts;
+      const uint64_t most = parts == 1 ? all : min(all + all / 4 + 64u, (uint32_t)T);
       if (st_cur + most > st_end) {  // uniform
         const uint64_t want = staging_want(a, most, st_end, G);
         if (tid == 0) s_chunk = atomicAdd(a.st_cursor, (unsigned long long)want);
@@ -1073,7 +1074,7 @@ __global__ __launch_bounds__(kOwnThreads, kOwnThreads * kOwnBlocksPerCU / 256) v
   }
   const uint64_t row0 = base + done;
   if (!a.st_fixed) {
-    fits = row0 + rows <= a.st_cap;
+    fits = row0 + rows <= (st_end < a.st_cap ? st_end : a.st_cap);
     st_cur += rows;
   }
   done += rows;

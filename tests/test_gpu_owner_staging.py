@@ -79,3 +79,30 @@ def test_every_window_a_row(kh, sctx, n, cover, k):
         want.free()
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("times", [1.1, 2.5])
+def test_parts_fit_staging(kh, octx, sctx, times):
+    """Unscreened owners counted in parts (600, of one-time keys nearly all) take
+    room for the rows they have, not for a table full of them."""
+    import torch
+    k, owners, n = 21, 600, int(times * 4608)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(int(10 * times))
+    # AAAAA, five bases that name the owner, ten of the key, G: canonical
+    ident = torch.randperm(1024, generator=g, device="cuda")[:owners].repeat_interleave(n)
+    key = torch.randint(0, 4 ** 10, (owners * n,), generator=g, device="cuda")
+    cols = [torch.zeros_like(key)] * 5 + [ident >> 2 * j & 3 for j in range(5)]
+    cols += [key >> 2 * j & 3 for j in range(10)] + [torch.full_like(key, 2)]
+    code = torch.stack(cols, 1)[torch.randperm(owners * n, generator=g, device="cuda")]
+    letters = torch.tensor([65, 67, 71, 84], dtype=torch.uint8, device="cuda")
+    seq = letters[code].reshape(-1).contiguous()
+    reads = kh.DeviceReads(seq, torch.full_like(seq, 73),
+                           torch.arange(owners * n + 1, device="cuda") * k)
+    table = octx.count(reads, k, use_bloom=False)
+    assert octx.stats()["rebuilds"] == 0
+    assert octx.stats()["table_bytes"] == 16 * owners * n
+    want = sctx.count(reads, k, use_bloom=False)
+    assert_same_table(table.to_numpy(), want.to_numpy())
+    table.free()
+    want.free()
