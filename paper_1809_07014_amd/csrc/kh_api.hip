@@ -454,14 +454,21 @@ int kh::finish_rows(kh_ctx* ctx, unsigned long long* ctr, uint8_t* table,
     KH_TRY(fetch(ctx, s, {c, ctr, sizeof c}));
     if (c[kCtrStatus] & kStatusLongTies) {
       // many keys share their top 20 bases: sort by the full key instead, and
-      // gather again
+      // gather again.  The rows' own keys and tallies, gathered anew, hold the
+      // keys meanwhile (a tally takes 32 bytes, a key up to 32); the caller's
+      // buffers need not be aligned for them.
       Buf<uint64_t> ka(pool), kb(pool);
-      KH_TRY(ka.alloc((uint64_t)rows * W));
-      KH_TRY(kb.alloc((uint64_t)rows * W));
+      uint64_t *x = keys.p, *y = reinterpret_cast<uint64_t*>(ext.p);
+      if (to_caller) {
+        KH_TRY(ka.alloc((uint64_t)rows * W));
+        KH_TRY(kb.alloc((uint64_t)rows * W));
+        x = ka.p;
+        y = kb.p;
+      }
       uint32_t* other = idx_sorted == idx_a.p ? idx_b.p : idx_a.p;
-      launch_row_keys(idx_sorted, rows, table, k, ka.p, s);
+      launch_row_keys(idx_sorted, rows, table, k, x, s);
       const int bits0 = 2 * (int)k - 64 * (W - 1);
-      if (radix_sort(ka.p, idx_sorted, kb.p, other, rows, W, bits0, tmp.p, s)) ga.idx = other;
+      if (radix_sort(x, idx_sorted, y, other, rows, W, bits0, tmp.p, s)) ga.idx = other;
       launch_gather(ga, s);
       HIP_TRY(hipGetLastError());
       HIP_TRY(hipStreamSynchronize(s));
