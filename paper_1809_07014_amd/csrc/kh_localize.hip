@@ -16,8 +16,8 @@
 //
 // Method.  One thread per read rolls the window's forward and
 // reverse-complement values base by base and looks the canonical value up in
-// the sorted rows, through an index of them by their top bits, until a window
-// hits; an LSD radix sort over the key's significant bits orders the read
+// the sorted rows, through an index of them by their top bits (but for very few
+// reads), until a window hits; an LSD radix sort over the key's significant bits orders the read
 // indices.  A second call gathers the reads' bytes in that order (16 lanes
 // per read, shared with the minimizer reordering).
 #include <algorithm>
@@ -50,10 +50,10 @@ __device__ __forceinline__ int base_or_bad(uint8_t c) {
 // 2.4 ms (3.1 ms without the masks, 15.6 ms with a binary search over all rows
 // per window and a byte load per base).  Several windows at a time, by one
 // thread or by sixteen, are slower: they look up windows past the first hit.
-template <int W>
+template <int W, class Index>
 __global__ __launch_bounds__(kLB) void k_anchor(const uint8_t* seq, const int64_t* offsets,
                                                 int64_t n_reads, uint32_t k,
-                                                const uint64_t* keys, MaskedIndex ix,
+                                                const uint64_t* keys, Index ix,
                                                 const uint32_t* row_contig, uint32_t none,
                                                 uint64_t* key_out, uint32_t* idx_out) {
   const int64_t r = (int64_t)blockIdx.x * kLB + threadIdx.x;
@@ -154,10 +154,27 @@ int localize_w(kh_ctx* ctx, const kh_table* t, const kh_contigs* c, const uint8_
   const uint32_t none = (uint32_t)c->n_contigs;
   Buf<uint32_t> start(pool);
   Buf<uint64_t> entry(pool);
-  MaskedIndex ix{};
-  KH_TRY(masked_index_build(pool, t->keys, t->n_rows, t->k, start, entry, &ix, s));
-  hipLaunchKernelGGL((k_anchor<W>), dim3(lgrid(n)), dim3(kLB), 0, s, seq, offs, n, c->k,
-                     t->keys, ix, c->row_contig, none, ka.p, ia.p);
+  auto anchors = [&](auto ix) {
+    hipLaunchKernelGGL((k_anchor<W, decltype(ix)>), dim3(lgrid(n)), dim3(kLB), 0, s, seq, offs, n,
+                       c->k, t->keys, ix, c->row_contig, none, ka.p, ia.p);
+  };
+  // An index takes a pass over the rows' keys, its masks another: few reads find
+  // their rows by searching them all, more by the index alone.  Reads of the
+  // table's own against 6.5e7 rows (k = 21), all rows / index / masks: 100 reads
+  // 0.25 / 0.36 / 0.63 ms, 300 0.79 / 0.57 / 0.79, 1e6 3.9 / 1.26 / 1.37 (foreign
+  // ones 27 / 7.5 / 3.7), 4e6 18.4 / 4.5 / 4.0; 10 and 30 reads against 3.1e6 rows
+  // (k = 33): 0.11 / 0.12 / 0.15 and 0.30 / 0.18 / 0.21.
+  if (n < t->n_rows >> 18) {
+    anchors(AllRows{t->n_rows});
+  } else if (n < t->n_rows >> 6) {
+    RowIndex ix{};
+    KH_TRY(row_index_build(pool, t->keys, t->n_rows, t->k, start, &ix, s));
+    anchors(ix);
+  } else {
+    MaskedIndex ix{};
+    KH_TRY(masked_index_build(pool, t->keys, t->n_rows, t->k, start, entry, &ix, s));
+    anchors(ix);
+  }
   HIP_TRY(hipGetLastError());
   const int which = radix_sort(ka.p, ia.p, kb.p, ib.p, n, 1, bit_width(none), tmp.p, s);
   HIP_TRY(hipGetLastError());

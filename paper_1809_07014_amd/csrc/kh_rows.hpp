@@ -70,12 +70,10 @@ __device__ __forceinline__ uint32_t row_prefix(const uint64_t* w, int top, int b
   return (uint32_t)((w[0] << low) | (w[W > 1 ? 1 : 0] >> (64 - low)));
 }
 
-// Row of key q, or -1.
+// Row of key q among the sorted rows [lo, hi), or -1.
 template <int W>
-__device__ __forceinline__ int64_t find_row(const uint64_t* keys, const RowIndex& ix, int top,
-                                            const uint64_t (&q)[W]) {
-  const uint32_t p = row_prefix<W>(q, top, ix.bits);
-  int64_t lo = ix.start[p], hi = ix.start[(uint64_t)p + 1];
+__device__ __forceinline__ int64_t find_between(const uint64_t* keys, int64_t lo, int64_t hi,
+                                                const uint64_t (&q)[W]) {
   while (lo < hi) {
     const int64_t mid = lo + (hi - lo) / 2;
     uint64_t w[W];  // the whole row at once: one round trip per probe
@@ -89,6 +87,25 @@ __device__ __forceinline__ int64_t find_row(const uint64_t* keys, const RowIndex
       hi = mid;
   }
   return -1;
+}
+
+// Row of key q, or -1.
+template <int W>
+__device__ __forceinline__ int64_t find_row(const uint64_t* keys, const RowIndex& ix, int top,
+                                            const uint64_t (&q)[W]) {
+  const uint32_t p = row_prefix<W>(q, top, ix.bits);
+  return find_between<W>(keys, ix.start[p], ix.start[(uint64_t)p + 1], q);
+}
+
+// No index: all n rows.
+struct AllRows {
+  int64_t n;
+};
+
+template <int W>
+__device__ __forceinline__ int64_t find_row(const uint64_t* keys, const AllRows& rows, int,
+                                            const uint64_t (&q)[W]) {
+  return find_between<W>(keys, 0, rows.n, q);
 }
 
 // The index with, beside each entry's first row, a bit per next key digit
@@ -105,21 +122,9 @@ __device__ __forceinline__ int64_t find_row(const uint64_t* keys, const MaskedIn
   const uint32_t p = row_prefix<W>(q, top, ix.bits + ix.sub);
   const uint64_t b = p >> ix.sub;
   const uint2 x = ix.entry[b];
-  int64_t lo = x.x, hi = ix.entry[b + 1].x;
+  const int64_t hi = ix.entry[b + 1].x;
   if (!((x.y >> (p & ((1u << ix.sub) - 1u))) & 1u)) return -1;
-  while (lo < hi) {
-    const int64_t mid = lo + (hi - lo) / 2;
-    uint64_t w[W];
-#pragma unroll
-    for (int j = 0; j < W; ++j) w[j] = keys[mid * W + j];
-    const int c = cmp_rows<W>(w, q);
-    if (c == 0) return mid;
-    if (c < 0)
-      lo = mid + 1;
-    else
-      hi = mid;
-  }
-  return -1;
+  return find_between<W>(keys, x.x, hi, q);
 }
 
 }  // namespace kh
