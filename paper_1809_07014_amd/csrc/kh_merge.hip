@@ -171,8 +171,8 @@ __global__ __launch_bounds__(kMB) void k_merge_place_contigs(
 unsigned mgrid(int64_t n) { return (unsigned)((n + kMB - 1) / kMB); }
 
 template <int W>
-int merge_rows(kh_ctx* ctx, const kh_table* t, const RowIndex& ix, const kh_table* c,
-               hipStream_t s, kh_table* out) {
+int merge_rows(kh_ctx* ctx, const kh_table* t, const RowIndex& ix, Buf<uint32_t>& start,
+               const kh_table* c, hipStream_t s, kh_table* out) {
   Pool* pool = &ctx->pool;
   const int64_t nt = t->n_rows, nc = c->n_rows, n = nt + nc;
   Buf<int64_t> cpos(pool);
@@ -180,15 +180,16 @@ int merge_rows(kh_ctx* ctx, const kh_table* t, const RowIndex& ix, const kh_tabl
   Buf<uint32_t> counts(pool), ext(pool);
   Buf<uint8_t> codes(pool);
   KH_TRY(cpos.alloc(nc + 1));
-  KH_TRY(keys.alloc((uint64_t)n * W));
-  KH_TRY(counts.alloc((uint64_t)n));
-  KH_TRY(ext.alloc((uint64_t)n * 8));
-  KH_TRY(codes.alloc((uint64_t)n * 2));
   if (nc > 0) {
     hipLaunchKernelGGL((k_merge_probe<W>), dim3(mgrid(nc)), dim3(kMB), 0, s, t->keys, ix,
                        2 * (int)t->k - 64 * (W - 1), c->keys, nc, cpos.p);
     HIP_TRY(hipGetLastError());
   }
+  start.reset();  // the index gives way to the merged rows
+  KH_TRY(keys.alloc((uint64_t)n * W));
+  KH_TRY(counts.alloc((uint64_t)n));
+  KH_TRY(ext.alloc((uint64_t)n * 8));
+  KH_TRY(codes.alloc((uint64_t)n * 2));
   if (nt > 0) {
     hipLaunchKernelGGL((k_merge_place_table<W>), dim3(mgrid(nt)), dim3(kMB), 0, s, t->keys,
                        t->counts, t->ext, t->codes, nt, cpos.p, nc, keys.p, counts.p, ext.p,
@@ -281,10 +282,10 @@ extern "C" int kh_merge_contigs(kh_ctx* ctx, const kh_table* t, const char* seq,
   int rc = make_table(ctx, t->k, &m);
   if (rc == KH_OK) {
     switch ((t->k + 31) / 32) {
-      case 1: rc = merge_rows<1>(ctx, t, ix, c, s, m); break;
-      case 2: rc = merge_rows<2>(ctx, t, ix, c, s, m); break;
-      case 3: rc = merge_rows<3>(ctx, t, ix, c, s, m); break;
-      default: rc = merge_rows<4>(ctx, t, ix, c, s, m); break;
+      case 1: rc = merge_rows<1>(ctx, t, ix, start, c, s, m); break;
+      case 2: rc = merge_rows<2>(ctx, t, ix, start, c, s, m); break;
+      case 3: rc = merge_rows<3>(ctx, t, ix, start, c, s, m); break;
+      default: rc = merge_rows<4>(ctx, t, ix, start, c, s, m); break;
     }
   }
   kh_table_free(c);
