@@ -418,6 +418,9 @@ int prune_w(kh_ctx* ctx, const kh_table* t, const kh_contigs* c, double alpha, d
   if (removed_host)
     HIP_TRY(hipMemcpy(removed_host, removed.p, (size_t)nc * 4, hipMemcpyDeviceToHost));
   // ---- compaction of the kept contigs, in their order
+  mean.reset();
+  cand.reset();
+  nbr.reset();
   Buf<uint64_t> keep(pool), lens(pool), idx(pool), noff(pool);
   KH_TRY(keep.alloc(nc));
   KH_TRY(lens.alloc(nc));

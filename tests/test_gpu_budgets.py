@@ -1,6 +1,7 @@
 """Calls in a context whose budget holds what they cannot do without (their
 inputs live in another context) and little beside: merging, pruning and counting
 on the owner path, against a context without a budget."""
+import numpy as np
 import pytest
 
 from brute import assert_same_table
@@ -63,4 +64,30 @@ def test_merge_holds_the_merged_rows(kh, free_ctx, k, contigs):
     finally:
         ctx.close()
     want.free()
+    table.free()
+
+
+def test_prune_memory(kh, free_ctx):
+    """47 bytes a contig for the sweeps, 32 for the kept ones' places, the kept
+    ones, and a quarter of a megabyte."""
+    table = free_ctx.count(_reads(kh, 60_000, 10, err=0.01), 21, min_count=1)
+    contigs = free_ctx.traverse(table)
+    nc = contigs.info()["n_contigs"]
+    want, report = free_ctx.prune(table, contigs)
+    kept, bases = want.info()["n_contigs"], want.info()["total_bases"]
+    assert nc > 1_000_000 and kept < nc
+    budget = _blocks(8 * nc, nc, nc, nc, 32 * nc, 4 * nc, 8 * nc, 8 * nc, 8 * nc, 8 * nc,
+                     8 * kept, 8 * kept, 8 * kept, kept, bases) + MIB // 4
+    ctx = _budgeted(kh, budget)
+    try:
+        got, rep = ctx.prune(table, contigs)
+        assert rep == report
+        a, b = got.to_numpy(), want.to_numpy()
+        for f in a:
+            np.testing.assert_array_equal(a[f], b[f])
+        got.free()
+    finally:
+        ctx.close()
+    want.free()
+    contigs.free()
     table.free()
