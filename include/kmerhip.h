@@ -436,9 +436,9 @@ typedef struct {
                                 owners' keys do not fit their LDS tables
                                 even after two finer splits, or whose two
                                 record buffers (16 x ceil((2k - min(10, 2k)
-                                + 6) / 64) bytes per window) and three bit
-                                planes (3/8 byte per base) the HBM budget
-                                refuses,
+                                + 6) / 64) bytes per window; first one of
+                                them and three bit planes, 3/8 byte per
+                                base) the HBM budget refuses,
                                 is counted with 0.  Not used by
                                 kh_count_noalloc, with aggregate = 1, or by
                                 serving.  0 or 1, default 1 */

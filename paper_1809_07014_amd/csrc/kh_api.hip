@@ -537,10 +537,6 @@ static int count_owned(kh_ctx* ctx, Packed& pk, const kh_params& p, hipStream_t 
   KH_TRY(h1.alloc((uint64_t)nb1 * grid + 1));
   KH_TRY(b1.alloc((uint64_t)nb1 + 1));
   KH_TRY(part.alloc(scan_tmp_words((int64_t)nb1 * grid + 1)));
-  Buf<uint64_t> win(pool), lx(pool), rx(pool);
-  KH_TRY(win.alloc((uint64_t)pk.plane_words));
-  KH_TRY(lx.alloc((uint64_t)pk.plane_words));
-  KH_TRY(rx.alloc((uint64_t)pk.plane_words));
   OwnRouteArgs ra{};
   ra.bases = pk.bases.p;
   ra.hq = pk.hq.p;
@@ -553,13 +549,26 @@ static int count_owned(kh_ctx* ctx, Packed& pk, const kh_params& p, hipStream_t 
   ra.shards = shards;
   ra.owner = p.owner;
   ra.p1 = (uint32_t)p1;
-  ra.win = win.p;
-  ra.lx = lx.p;
-  ra.rx = rx.p;
   ra.h1 = h1.p;
   ra.ctr = ctr;
+  // The windows' planes are kept up to the emit alone, so that the call needs no
+  // more memory than the records (and rows) do; one that emits again forms them
+  // again, in a record buffer that is free (room, of that many words) if it can.
+  Buf<uint64_t> win(pool);
+  const uint64_t pw = (uint64_t)pk.plane_words;
+  auto planes = [&](uint64_t* room, uint64_t words) -> int {
+    if (words < 3 * pw) {
+      KH_TRY(win.alloc(3 * pw));
+      room = win.p;
+    }
+    ra.win = room;
+    ra.lx = room + pw;
+    ra.rx = room + 2 * pw;
+    launch_own_planes(ra, s);
+    return KH_OK;
+  };
   mark(ctx, 2, s);
-  launch_own_planes(ra, s);
+  KH_TRY(planes(nullptr, 0));
   launch_own_hist(ra, grid, s);
   exclusive_scan_u32(h1.p, (int64_t)nb1 * grid + 1, part.p, s);
   launch_gather_strided(h1.p, (uint64_t)grid, (uint32_t)nb1 + 1, b1.p, s);
@@ -590,10 +599,11 @@ static int count_owned(kh_ctx* ctx, Packed& pk, const kh_params& p, hipStream_t 
   // ---- level 1 emit
   Buf<uint64_t> rec1(pool), rec2(pool);
   KH_TRY(rec1.alloc(n_rec * R));
-  KH_TRY(rec2.alloc(n_rec * R));
   ra.rec = rec1.p;
   launch_own_emit(ra, grid, s);
   HIP_TRY(hipGetLastError());
+  win.reset();
+  KH_TRY(rec2.alloc(n_rec * R));
 
   // ---- level 2 and the owners; a failed fit splits the owners finer
   const int chunk = own_chunk_records(k);
@@ -617,7 +627,11 @@ static int count_owned(kh_ctx* ctx, Packed& pk, const kh_params& p, hipStream_t 
   const int p2max = std::max(0, std::min(kOwnL2Max, 2 * (int)k - p1));
   for (int attempt = 0;; ++attempt) {
     // the previous attempt staged its rows over the level-1 records
-    if (attempt > 0) launch_own_emit(ra, grid, s);
+    if (attempt > 0) {
+      KH_TRY(planes(rec2.p, n_rec * R));
+      launch_own_emit(ra, grid, s);
+      win.reset();
+    }
     std::vector<OwnBucket> bk(nb1);
     uint64_t n_owners = 0, n_chunks = 0, m_size = 0;
     for (int b = 0; b < nb1; ++b) {
@@ -835,6 +849,7 @@ static int count_owned(kh_ctx* ctx, Packed& pk, const kh_params& p, hipStream_t 
     Buf<uint64_t> keys(pool);
     const bool to_caller = t->dst_cap >= 0;
     if (!to_caller) {
+      pool->make_room((uint64_t)rows * rb);
       KH_TRY(keys.alloc((uint64_t)rows * W));
       KH_TRY(counts.alloc((uint64_t)rows));
       KH_TRY(ext.alloc((uint64_t)rows * 8));

@@ -186,6 +186,14 @@ struct Pool {
     cached_bytes = 0;
   }
 
+  // Blocks of `bytes` in all are asked for next: where the budget does not hold
+  // them beside the free blocks these go at once, before one is taken for a
+  // request that it is much too large for.
+  void make_room(uint64_t bytes) {
+    std::lock_guard<std::recursive_mutex> lk(mu);
+    if (budget && held + bytes > budget) drop_cached();
+  }
+
   int get(void** out, uint64_t bytes) {
     std::lock_guard<std::recursive_mutex> lk(mu);
     if (arena) return arena_get(out, bytes);

@@ -91,3 +91,27 @@ def test_prune_memory(kh, free_ctx):
     want.free()
     contigs.free()
     table.free()
+
+
+@pytest.mark.parametrize("k", [21, 55])
+def test_owner_count_holds_records_and_rows(kh, free_ctx, k):
+    """The packed reads, two record buffers, the rows, and 24 MiB (a third
+    of what the windows' planes take beside them while they are routed)."""
+    n, length = 1_300_000, 150
+    reads = _reads(kh, n, 20)
+    want = free_ctx.count(reads, k)
+    rows, W, R = want.info()["n_rows"], (k + 31) // 32, (2 * k - 10 + 6 + 63) // 64
+    bases = n * length
+    records = 8 * R * n * (length + 1 - k)
+    plane = bases // 8
+    assert 3 * plane > 69 * MIB
+    ctx = _budgeted(kh, _blocks(2 * plane, plane, plane, plane, records, records, 8 * W * rows,
+                                4 * rows, 32 * rows, 2 * rows) + 24 * MIB)
+    try:
+        got = ctx.count(reads, k)
+        assert ctx.stats()["table_bytes"] == 2 * records  # the owner path, staging in them
+        assert_same_table(got.to_numpy(), want.to_numpy())
+        got.free()
+    finally:
+        ctx.close()
+    want.free()
