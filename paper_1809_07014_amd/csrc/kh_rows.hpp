@@ -97,7 +97,8 @@ __device__ __forceinline__ int64_t find_row(const uint64_t* keys, const RowIndex
   return find_between<W>(keys, ix.start[p], ix.start[(uint64_t)p + 1], q);
 }
 
-// No index: all n rows.
+// No index: all n rows.  Some 26 probes, one after another, and few of them
+// equal: the plain search looks at no more of a row than decides its side.
 struct AllRows {
   int64_t n;
 };
@@ -105,7 +106,8 @@ struct AllRows {
 template <int W>
 __device__ __forceinline__ int64_t find_row(const uint64_t* keys, const AllRows& rows, int,
                                             const uint64_t (&q)[W]) {
-  return find_between<W>(keys, 0, rows.n, q);
+  const int64_t r = lower_bound_rows<W>(keys, rows.n, q);
+  return r < rows.n && cmp_rows<W>(keys + r * W, q) == 0 ? r : -1;
 }
 
 // The index with, beside each entry's first row, a bit per next key digit
