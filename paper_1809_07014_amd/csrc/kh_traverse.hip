@@ -636,11 +636,11 @@ unsigned grid(int64_t n) { return (unsigned)((n + kTB - 1) / kTB); }
 // One k-mer in mask + 1 is a splitter.  Longer stretches mean fewer records to
 // rank and place; shorter ones more walkers in flight and a shorter longest
 // walk (about log(walkers) times the mean), which is what a small table waits
-// for.  1.5e6 rows: walk 281 us at one in 64, 171 at 32, 128 at 16, 99 at 4,
-// where the jumps take 134 us instead of 60 and the places 88 instead of 30;
-// 1.6e8 rows: walk 15.3 ms at 64, 15.5 at 32, 17.0 at 16, and the ranks and
-// places 2.6, 4.0 and 7.2 ms.
-uint32_t sample_mask(int64_t n) { return n < (1 << 24) ? 15u : n < (1 << 26) ? 31u : 63u; }
+// for.  The call at one in 16 / 32 / 64 (k = 21): 5.9e5 rows 0.39 / 0.44 / 0.52
+// ms, 2.0e6 0.64 / 0.62 / 0.71, 1.1e7 2.20 / 2.09 / 2.11, 1.6e7 3.14 / 2.89 /
+// 2.93, 2.1e7 4.34 / 3.98 / 3.92, 6.8e7 17.4 / 16.0 / 15.4, 1.6e8 46.1 / 41.3 /
+// 39.2 (one in 8 is slower throughout, one in 128 up to 6.8e7 rows).
+uint32_t sample_mask(int64_t n) { return n < (3 << 19) ? 15u : n < (1 << 24) ? 31u : 63u; }
 
 template <int W, typename S>
 int traverse_ws(kh_ctx* ctx, const kh_table* t, hipStream_t s, kh_contigs* out) {
