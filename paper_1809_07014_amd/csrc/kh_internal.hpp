@@ -164,7 +164,7 @@ struct GatherArgs {
 
 // ---- owner-partitioned counting (kh_owner.hip) ----
 constexpr int kOwnL1Max = 1024;       // level-1 buckets at most (p1 <= 10)
-constexpr int kOwnRouteThreads = 1024;  // level-1 block: one window per lane per tile
+constexpr int kOwnRouteThreads = 1024;  // level-1 block: four windows per lane per tile
 constexpr int kOwnL2Max = 11;         // level-2 digit bits at most
 constexpr int kOwnPartThreads = 1024;  // level-2 partition block
 constexpr int kOwnThreads = 1024;      // owner block
