@@ -165,15 +165,18 @@ __global__ void k_mark_starts(const int64_t* __restrict__ off, int64_t n_reads,
 }
 
 void launch_pack_range(const PackArgs& a, int64_t p0, int64_t p1, hipStream_t s) {
-  const int64_t threads = (p1 - p0 + 63) / 64 * 4;
-  if (threads <= 0) return;
   const int64_t least = (int64_t)a.qual_offset + a.qual_cutoff;
   const int q_min = (int)(least < 0 ? 0 : least > 256 ? 256 : least);
-  hipLaunchKernelGGL(k_pack, dim3((unsigned)((threads + kBlock - 1) / kBlock)), dim3(kBlock), 0,
-                     s, a.seq + p0, a.qual + p0, p1 - p0, q_min,
-                     reinterpret_cast<uint32_t*>(a.bases + p0 / 32),
-                     reinterpret_cast<uint16_t*>(a.hq + p0 / 64),
-                     reinterpret_cast<uint16_t*>(a.bad + p0 / 64));
+  // a launch holds under 2^32 threads: at most 2^34 positions in each
+  for (int64_t q0 = p0; q0 < p1; q0 += 1ll << 34) {
+    const int64_t len = p1 - q0 < (1ll << 34) ? p1 - q0 : 1ll << 34;
+    const int64_t threads = (len + 63) / 64 * 4;
+    hipLaunchKernelGGL(k_pack, dim3((unsigned)((threads + kBlock - 1) / kBlock)), dim3(kBlock), 0,
+                       s, a.seq + q0, a.qual + q0, len, q_min,
+                       reinterpret_cast<uint32_t*>(a.bases + q0 / 32),
+                       reinterpret_cast<uint16_t*>(a.hq + q0 / 64),
+                       reinterpret_cast<uint16_t*>(a.bad + q0 / 64));
+  }
 }
 
 void launch_pack(const PackArgs& a, hipStream_t s) {
