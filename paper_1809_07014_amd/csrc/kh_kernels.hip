@@ -251,6 +251,17 @@ __device__ __forceinline__ uint8_t* find_or_claim(uint8_t* __restrict__ table,
   return nullptr;
 }
 
+// The slot's count has come to kHeavyCount (and does again every 2^16
+// occurrences): mark it.  Right tally T lies right below the mark, and a carry
+// out of it would clear the mark: so occurrences from there on leave the spill
+// tallies alone (the recount has them all), and T's, which those that find the
+// wrapped count below kHeavyCount still add to, starts again from 0.
+__device__ __forceinline__ void mark_heavy(uint8_t* slot, const SlotLayout& lay) {
+  uint64_t* sr = reinterpret_cast<uint64_t*>(slot + lay.sr_off);
+  __hip_atomic_fetch_and(sr, ~(0x7fffull << 48), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_fetch_or(sr, kHeavyBit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Bloom word of a key and its pattern of up to four bits within a 32-bit
 // half, from a hash independent of the table position.  Level 1 ("seen")
 // uses the low half of the word, level 2 ("seen twice") the high half, so
@@ -508,7 +519,7 @@ __device__ __forceinline__ void tile_pass(
     for (int j = 0; j < J; ++j) {  // spill occurrences also count exactly
       if (!sp[j]) continue;
       const uint32_t c = (uint32_t)(oldx[j] & kCountMask);
-      if (c < kSpillAt) continue;
+      if (c < kSpillAt || c >= kHeavyCount) continue;
       if (L[j] >= 0)
         __hip_atomic_fetch_add(reinterpret_cast<uint64_t*>(sp[j] + lay.sl_off),
                                1ull << (16 * L[j]), __ATOMIC_RELAXED,
@@ -517,9 +528,7 @@ __device__ __forceinline__ void tile_pass(
         __hip_atomic_fetch_add(reinterpret_cast<uint64_t*>(sp[j] + lay.sr_off),
                                1ull << (16 * R[j]), __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
-      if (c == kHeavyCount - 1)  // once per 2^16 occurrences: mark heavy
-        __hip_atomic_fetch_or(reinterpret_cast<uint64_t*>(sp[j] + lay.sr_off),
-                              kHeavyBit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (c == kHeavyCount - 1) mark_heavy(sp[j], lay);
     }
   }
 
@@ -656,8 +665,11 @@ __device__ __forceinline__ void agg_update(uint8_t* sp, const SlotLayout& lay, u
   const uint64_t old = __hip_atomic_fetch_add(reinterpret_cast<uint64_t*>(sp + lay.x_off), inc,
                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const uint32_t c = (uint32_t)(old & kCountMask);
-  const uint32_t keep = c < kSpillAt ? min(m, kSpillAt - c) : 0u;  // non-spill occurrences
-  if (keep < m) {
+  // Non-spill occurrences.  (Written so that the difference never wraps: with
+  // `c < kSpillAt ? min(m, kSpillAt - c) : 0` the compiler took c <= kSpillAt
+  // for granted below and dropped the comparison with kHeavyCount.)
+  const uint32_t keep = min(m, kSpillAt - min(c, kSpillAt));
+  if (keep < m && c < kHeavyCount) {
     // spill tallies: at least (tallies - keep) per side, taken base by base
     uint32_t need_l = sl > keep ? sl - keep : 0u, need_r = sr > keep ? sr - keep : 0u;
     uint64_t add_l = 0, add_r = 0;
@@ -678,8 +690,7 @@ __device__ __forceinline__ void agg_update(uint8_t* sp, const SlotLayout& lay, u
   }
   // an occurrence at count kHeavyCount - 1 (mod 2^16) marks the k-mer heavy
   if (((kHeavyCount - 1u - c) & 0xffffu) < m)
-    __hip_atomic_fetch_or(reinterpret_cast<uint64_t*>(sp + lay.sr_off), kHeavyBit,
-                          __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    mark_heavy(sp, lay);
 }
 
 template <int W>
@@ -1041,16 +1052,14 @@ __global__ __launch_bounds__(kBlock) void k_replay(const TileDesc* __restrict__ 
                                               x_increment(L, R), __ATOMIC_RELAXED,
                                               __HIP_MEMORY_SCOPE_AGENT);
   const uint32_t c = (uint32_t)(old & kCountMask);
-  if (c >= kSpillAt) {
+  if (c >= kSpillAt && c < kHeavyCount) {
     if (L >= 0)
       __hip_atomic_fetch_add(reinterpret_cast<uint64_t*>(sp + lay.sl_off), 1ull << (16 * L),
                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (R >= 0)
       __hip_atomic_fetch_add(reinterpret_cast<uint64_t*>(sp + lay.sr_off), 1ull << (16 * R),
                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (c == kHeavyCount - 1)
-      __hip_atomic_fetch_or(reinterpret_cast<uint64_t*>(sp + lay.sr_off), kHeavyBit,
-                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (c == kHeavyCount - 1) mark_heavy(sp, lay);
   }
 }
 
